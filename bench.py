@@ -126,7 +126,7 @@ def kernel_sources(workload: str) -> list:
     if workload in KERNEL_FAMILY:
         fam = KERNEL_FAMILY[workload]
     elif workload.endswith(("_q8", "_q4")):
-        fam = "tvl_quant.hip"
+        return [*KERNEL_COMMON, "tvl_quant_device.h", "tvl_quant_split.hip"]
     else:
         fam = "tvl_gemv.hip"
     return [*KERNEL_COMMON, fam]

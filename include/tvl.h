@@ -154,8 +154,11 @@ typedef enum tvl_status {
  * One launch (plan or batch) may hold plain fp32/fp16 items together with
  * ONE of: RMSNorm/SwiGLU items, several-vector items, quantised items.
  * Items with g != NULL, op != TVL_OP_GEMV or nrhs > 1 run in direct-x mode;
- * they and quantised items cannot be K-split.  Quantised items read x
- * directly too, or, with TVL_FLAG_X_LDS, from a copy of x that each
+ * they and quantised items take no `ksplit`.  In a launch whose items all hold
+ * codes of one width and that no tuning shapes, wavefronts of a workgroup
+ * share rows and split their columns (partial sums joined in a fixed order).
+ * In every other launch quantised items read x directly too, or, with
+ * TVL_FLAG_X_LDS, from a copy of x that each
  * workgroup stages in LDS once per row tile (x of the largest quantised K in
  * the launch, in whole KiB, must fit a workgroup's 160 KB: K <= 40,960;
  * else TVL_ERR_SHAPE); plain items in such a launch still read x directly. */
@@ -334,7 +337,7 @@ TVL_API tvl_status tvl_gemv_batch_sweep(const tvl_item *items, int32_t n,
 
 /* Sweep plan: validate `items`, build the tile table (tiles of R*W output
  * rows; R/2*W for SwiGLU items; R*W*64/G for quantised items whose rows use
- * G lanes each; ordered by bytes per tile, largest first; in plans with
+ * G lanes each, and 4 to 32 rows where they split the columns; ordered by bytes per tile, largest first; in plans with
  * several-vector or quantised items, each item's tiles are kept on as few
  * of the GPU's XCDs as the largest-first order allows, so each XCD's L2
  * fetches fewer x vectors) and upload it once.  The item

@@ -32,6 +32,7 @@ struct tvl_plan {
     int wmode = 0;  // weight dtypes: 0 fp32 only, 1 fp16 only, 2 both
     bool quant = false; // some item has block-quantised weights
     int qxbytes = 0;    // quantised plan with x in LDS: dynamic LDS per workgroup
+    tvl::QuantSplit qsplit; // waves > 0: the column-split quantised kernels
     Shape shape{4, 4, 2, tvl::kXLds};
     int ks_cap = 0;
     int ntiles = 0;
@@ -424,6 +425,65 @@ Shape default_quant_shape(double qbytes, bool q4, int64_t kq)
     return Shape{8, 4, 1, tvl::kXDirect};
 }
 
+// Launches whose items are all quantised to the same width take the column
+// split (tvl_quant_split.hip) unless a tuning says otherwise: `split`
+// wavefronts share each set of 256 / lanes rows.  Measured on MI355X against
+// the whole-row shapes above it wins at every size tried, from 256 x 256 to
+// the 7B token (us, 8-bit / 4-bit): 768 x 768 3.05 against 3.58 / 3.11 against
+// 7.73; 4096 x 11008 11.3 against 36.3 / 7.9 against 87.9; one 7B layer 35.6
+// against 53.5 / 22.3 against 93.4; 110M token 19.7 against 22.2 / 13.8
+// against 15.8; 7B token 966 against 986 / 545 against 584.
+//   - Long launches: the fewest lanes per row (16 of 16 columns, 8 of 32: 256
+//     columns per chunk), whose x is read from LDS by the most rows.  Two
+//     wavefronts per row set where rows are short (8-bit: mean K below 2048;
+//     4-bit, where the decode and not the loads bounds the wavefront: 8192)
+//     and the launch still has 12 wavefronts per CU, else four: 110M token,
+//     8-bit, 19.7 us with two against 26 with four; 7B token 994 against 966.
+//   - Fewer wavefronts than 12 per CU (8 for 4-bit codes, whose wavefronts
+//     decode twice the codes per byte): twice the lanes per row as long as
+//     four chunks per row are left and no row pads past 5/4 of its loads
+//     (4096 x 4096, 8-bit: 5.7 us with 32 lanes against 6.1 with 16; 1024 x
+//     8192: 4.3 with 64 against 7.0).
+tvl::QuantSplit quant_split(const tvl_item *items, int32_t n, int cus)
+{
+    tvl::QuantSplit s;
+    double codes = 0, kcodes = 0, rows = 0;
+    for (int32_t i = 0; i < n; ++i) {
+        if (!is_quant(items[i].dtype) || items[i].dtype != items[0].dtype) return s;
+        const double c = (double)items[i].M * (double)items[i].K;
+        codes += c;
+        kcodes += c * (double)items[i].K;
+        rows += (double)items[i].M;
+    }
+    if (n < 1) return s;
+    s.bits = quant_bits(items[0].dtype);
+    const double kmean = kcodes / codes;
+    s.lanes = s.bits == 8 ? 16 : 8;
+    auto waves = [&] { return rows * s.lanes * s.split / 256; };
+    s.split = 2;
+    if (waves() >= 12.0 * cus && kmean < (s.bits == 8 ? 2048.0 : 8192.0)) {
+        s.waves = s.bits == 8 ? 4 : 2;
+        return s;
+    }
+    s.split = s.waves = 4;
+    while (s.lanes < 64 && waves() < (s.bits == 8 ? 12.0 : 8.0) * cus) {
+        const int g = 2 * s.lanes;
+        for (int32_t i = 0; i < n; ++i) {
+            const int64_t nv = (items[i].K * s.bits + 127) / 128;
+            if (nv < 4 * g || (nv + g - 1) / g * g * 4 > nv * 5) return s;
+        }
+        s.lanes = g;
+    }
+    return s;
+}
+
+// A tuning that chooses the kernel: any field but ksplit, which only says
+// that there is none.
+bool tunes(const tvl_tuning *t)
+{
+    return t && (t->rows_per_wave || t->waves_per_block || t->unroll || t->grid || t->flags);
+}
+
 Shape default_shape_items(const tvl_item *items, int32_t n)
 {
     double b16 = 0, b32 = 0, row32 = 0;
@@ -671,6 +731,7 @@ tvl_status plan_build(const tvl_item *items, int32_t n, const tvl_tuning *tuning
     p->qxbytes = qxbytes;
     p->multiB = multiB;
     p->wmode = f32 && f16 ? 2 : f16 ? 1 : 0;
+    if (quant && !tunes(tuning)) p->qsplit = quant_split(items, n, info.cus);
     // output rows per tile: a SwiGLU tile streams R rows of W and of W3 per
     // wavefront, i.e. R/2 output rows; a quantised item whose rows share a
     // wavefront in groups of G lanes covers 64 / G times R rows per wavefront
@@ -685,6 +746,7 @@ tvl_status plan_build(const tvl_item *items, int32_t n, const tvl_tuning *tuning
         return item_lanes(t, few_lanes && t.dtype == TVL_Q4);
     };
     auto rows_of = [&](const tvl_item &t) {
+        if (p->qsplit.waves) return p->qsplit.rows();
         return (t.op == TVL_OP_SWIGLU ? shape.R / 2 : shape.R) * shape.W * (64 / lanes_of(t));
     };
     // bytes per tile, largest first, so the longest tiles start first
@@ -753,7 +815,9 @@ tvl_status plan_launch(const tvl_plan *p, hipStream_t st)
 {
     if (p->ntiles == 0) return TVL_OK;
     const hipError_t e =
-        p->quant    ? tvl::launch_sweep_quant(p->shape, p->d_items, p->d_tiles, p->ntiles, p->grid,
+        p->qsplit.waves ? tvl::launch_sweep_quant_split(p->qsplit, p->d_items, p->d_tiles,
+                                                        p->ntiles, st)
+        : p->quant  ? tvl::launch_sweep_quant(p->shape, p->d_items, p->d_tiles, p->ntiles, p->grid,
                                               p->qxbytes, st)
         : p->multiB ? tvl::launch_sweep_multi(p->shape, p->multiB, p->wmode, p->d_items,
                                               p->d_tiles, p->ntiles, p->grid, st)
@@ -840,7 +904,10 @@ tvl_status gemv_impl(const void *W, int64_t ldw, int32_t dtype, const float *x, 
             st = noalloc_setup(qdev, stream, &p, &c);
             if (st != TVL_OK) return st;
         }
-        const hipError_t qe = tvl::launch_item_quant(qs, dev_item(it), qxbytes, stream);
+        const hipError_t qe =
+            tunes(tuning)
+                ? tvl::launch_item_quant(qs, dev_item(it), qxbytes, stream)
+                : tvl::launch_item_quant_split(quant_split(&it, 1, qinfo.cus), dev_item(it), stream);
         if (qe != hipSuccess) return fail_hip(qe, "quantised gemv launch");
         return TVL_OK;
     }
@@ -1039,7 +1106,8 @@ tvl_status tvl_sweep_plan_info(const tvl_plan *plan, int64_t *ntiles, int64_t *g
     if (!plan) return fail(TVL_ERR_NULL, "tvl_sweep_plan_info: plan is NULL");
     if (ntiles) *ntiles = plan->ntiles;
     if (grid) *grid = plan->grid;
-    if (rows_per_tile) *rows_per_tile = plan->shape.R * plan->shape.W;
+    if (rows_per_tile)
+        *rows_per_tile = plan->qsplit.waves ? plan->qsplit.rows() : plan->shape.R * plan->shape.W;
     return TVL_OK;
 }
 

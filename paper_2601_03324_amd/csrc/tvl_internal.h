@@ -139,6 +139,20 @@ hipError_t launch_sweep_quant(const Shape &s, const DevItem *items, const DevTil
                               int ntiles, int grid, int xbytes, hipStream_t st);
 hipError_t launch_item_quant(const Shape &s, const DevItem &item, int xbytes, hipStream_t st);
 
+// Launches whose items all hold `bits`-bit codes: `split` of a workgroup's
+// `waves` wavefronts share the columns of each set of 4 * 64 / lanes rows.
+// A launch without quant split has waves == 0.
+struct QuantSplit {
+    int bits = 0;
+    int lanes = 0;
+    int split = 0;
+    int waves = 0;
+    int rows() const { return 4 * (64 / lanes) * (waves / split); } // per tile
+};
+hipError_t launch_sweep_quant_split(const QuantSplit &s, const DevItem *items,
+                                    const DevTile *tiles, int ntiles, hipStream_t st);
+hipError_t launch_item_quant_split(const QuantSplit &s, const DevItem &item, hipStream_t st);
+
 // LDS bytes for x of K columns in the quantised kernels' layout: whole
 // 1 KiB blocks of 256 columns (the staging loads' unit; the ragged last load
 // of a row reads at most to the end of its 32-column run).

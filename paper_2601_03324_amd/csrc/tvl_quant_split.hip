@@ -1,0 +1,268 @@
+// tvl_quant_split.hip -- GEMV over block-quantised weights of one width: the
+// wavefronts of a workgroup share sets of rows and split their columns.  The
+// default for such launches (quant_split in tvl_abi.cpp, which says when it
+// takes how many lanes and wavefronts, and why).
+//
+// What bounds it: HBM in long launches, the decode's vector instructions next
+// (~2 per code), and in short ones the latency of a wavefront's dependent
+// loads, so a launch needs many wavefronts with little to do each.  With whole
+// rows per wavefront a 4096 x 11008 4-bit matrix had 16 workgroups of 43
+// dependent rounds (88 us); with the columns split over four wavefronts it has
+// 512 of 3 rounds (8.6 us).  A split also makes x cheap: each wavefront copies
+// just its own chunk's x into LDS (1-4 coalesced loads, no workgroup barrier),
+// where direct x costs as many load instructions as the codes.  So does the
+// register budget: x takes registers only while a chunk is decoded, which
+// leaves room for the next chunk's codes in flight at 4-5 wavefronts per SIMD
+// (8-bit 90, 4-bit 112 VGPRs; whole rows 119-145).  That is why the split wins
+// in long launches too: 7B token, 7.0 GB of 8-bit codes 983 -> 965 us (7.28
+// TB/s), 3.7 GB of 4-bit codes 584 -> 555 us (6.71 TB/s).
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "tvl_quant_device.h"
+
+namespace tvl {
+namespace {
+
+// One chunk of a row set: G lanes x 16 bytes of codes of each of the lane's R
+// rows, their scales, and the chunk's x (brought by all 64 lanes together).
+template <int BITS, int G, int R>
+struct SplitChunk {
+    static constexpr int N = 128 / BITS;     // columns per 16-byte load
+    static constexpr int NX = N / 4;         // float4 of x per load
+    static constexpr int CH = G * N;         // columns per chunk
+    static constexpr int XV = (CH / 4 + kWave - 1) / kWave; // float4 of x per lane to stage
+    u4 w[R];
+    float sc[R];
+    f4 x[XV];
+};
+
+// Keeps the LDS accesses before and after it in order for the compiler; the
+// hardware runs one wavefront's LDS accesses in order, so it costs nothing.
+__device__ __forceinline__ void wave_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Rows of one row set: 64 / G groups of R consecutive rows.  Every load's whole
+// offset is in the range-checked per-lane part, and lanes past the row's end
+// take an offset past every descriptor (no memory access, zeros): the ragged
+// last chunk needs no branch of its own.
+template <int BITS, int G, int R>
+struct SplitRows {
+    using C = SplitChunk<BITS, G, R>;
+    static constexpr int N = C::N, NX = C::NX, CH = C::CH, XV = C::XV;
+    static constexpr int kNone = (int)0x80000000u; // past any descriptor's end
+    __amdgpu_buffer_rsrc_t wr, sr, xr;
+    int vw[R], sblk, K, nv, seg, lane;
+    unsigned vs;
+    TVL_LDS float *xl; // this wavefront's x chunk (lds_x4's layout)
+
+    __device__ __forceinline__ SplitRows(const DevItem &it, int row0, int lane_, TVL_LDS float *xl_)
+        : K(it.K), nv((it.K + N - 1) / N), seg(lane_ % G), lane(lane_), xl(xl_)
+    {
+        const unsigned char *codes = static_cast<const unsigned char *>(it.W);
+        const int left = it.M - row0, sub = lane / G, ng = (it.K + 63) / 64;
+        const int64_t Mp = ((int64_t)it.M + 3) / 4 * 4;
+        wr = make_rsrc(codes + (int64_t)row0 * it.ldw, (int64_t)left * it.ldw);
+        sr = make_rsrc(codes + (int64_t)it.M * it.ldw, 4 * Mp * ng);
+        xr = make_rsrc(it.x, ((int64_t)it.K * 4 + 15) & ~(int64_t)15);
+#pragma unroll
+        for (int r = 0; r < R; ++r) // rows past M: computed from row M - 1, not stored
+            vw[r] = (int)(min(sub * R + r, left - 1) * it.ldw) + seg * 16;
+        const int srow0 = row0 + sub * R;
+        vs = 16u * ((unsigned)(srow0 / 4) * ng + seg * N / 64) + 4 * (srow0 % 4);
+        sblk = 16 * ng;
+    }
+
+    // (a chunk past the row's last loads nothing and gets zeros)
+    __device__ __forceinline__ void load(int c, C &t) const
+    {
+#pragma unroll
+        for (int i = 0; i < XV; ++i) {
+            const int j = lane + kWave * i; // float4 of the chunk
+            if (CH / 4 >= kWave || j < CH / 4)
+                t.x[i] = __builtin_bit_cast(
+                    f4, __builtin_amdgcn_raw_buffer_load_b128(xr, c * (CH * 4) + 16 * j, 0, 0));
+        }
+        const bool on = c * G + seg < nv;
+        const int ws = on ? c * (G * 16) : kNone;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            t.w[r] = __builtin_amdgcn_raw_buffer_load_b128(wr, on ? vw[r] + ws : kNone, 0, kBufNT);
+        const unsigned so = vs + c * (CH / 64 * 16);
+#pragma unroll
+        for (int q = 0; q < R / 4; ++q) {
+            const f4 v = __builtin_bit_cast(
+                f4, __builtin_amdgcn_raw_buffer_load_b128(sr, on ? (int)(so + sblk * q) : kNone, 0, 0));
+            t.sc[4 * q] = v.x;
+            t.sc[4 * q + 1] = v.y;
+            t.sc[4 * q + 2] = v.z;
+            t.sc[4 * q + 3] = v.w;
+        }
+    }
+
+    // x past K is set to zero: the last 16-byte piece may hold up to three
+    // values past it, and a lane's codes past K are padding
+    __device__ __forceinline__ void stage(int c, C &t) const
+    {
+        const bool ragged = (c + 1) * CH > K; // wavefront-uniform
+        wave_order(); // the previous chunk's x is read
+#pragma unroll
+        for (int i = 0; i < XV; ++i) {
+            const int j = lane + kWave * i;
+            if (CH / 4 < kWave && j >= CH / 4) continue;
+            if (ragged) t.x[i] = mask_from<f4, 4>(t.x[i], K - c * CH - 4 * j);
+            *(TVL_LDS f4 *)(xl + 4 * ((j & ~7) | ((j ^ (j >> 3)) & 7))) = t.x[i];
+        }
+        wave_order();
+    }
+
+    __device__ __forceinline__ void compute(const C &t, float (&acc)[R]) const
+    {
+        f4 xv[NX];
+#pragma unroll
+        for (int k = 0; k < NX; ++k)
+            xv[k] = lds_x4(xl, seg * N + 4 * k);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if constexpr (BITS == 4)
+                acc[r] = fmaf(t.sc[r] * 16.f, qdot4(t.w[r], xv), acc[r]);
+            else
+                acc[r] = fmaf(t.sc[r], qdot8(t.w[r], xv), acc[r]);
+            // one row's decode at a time, here and in no later block
+            asm volatile("" : "+v"(acc[r]));
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+
+    // Chunks c0, c0 + step, ... below the row's end: the next chunk's loads are
+    // issued before this one's decode.  The chunk's x goes through LDS within
+    // the wavefront.  Two chunks per turn, so that each has registers of its
+    // own and the loop copies none.
+    __device__ __forceinline__ void run(int c0, int step, float (&acc)[R]) const
+    {
+        const int nc = (nv + G - 1) / G;
+        C a, b;
+        int c = c0;
+        load(c, a);
+        for (; c + step < nc; c += 2 * step) {
+            stage(c, a);
+            __builtin_amdgcn_sched_barrier(0);
+            load(c + step, b);
+            __builtin_amdgcn_sched_barrier(0);
+            compute(a, acc);
+            stage(c + step, b);
+            __builtin_amdgcn_sched_barrier(0);
+            load(c + 2 * step, a);
+            __builtin_amdgcn_sched_barrier(0);
+            compute(b, acc);
+        }
+        if (c < nc) {
+            stage(c, a);
+            compute(a, acc);
+        }
+    }
+};
+
+// One tile: KS wavefronts share each set of ROWS rows and take its chunks in
+// turn, so the workgroup covers WV / KS sets.
+template <int BITS, int G, int R, int KS, int WV>
+__device__ __forceinline__ void tile_split(const DevItem &it, int row0, f4 *lds)
+{
+    constexpr int ROWS = R * (kWave / G);
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int wrow0 = row0 + wave / KS * ROWS;
+    float acc[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        acc[r] = 0.f;
+    if (wrow0 < it.M) { // wavefront-uniform
+        const SplitRows<BITS, G, R> rows(it, wrow0, lane,
+                                         (TVL_LDS float *)lds + wave * SplitRows<BITS, G, R>::CH);
+        rows.run(wave % KS, KS, acc);
+    }
+    const float v = reduce_group<R, G>(acc, lane);
+    constexpr int S = G / R; // lanes holding each row's total
+    const int r = (lane / G) * R + lane % G / S;
+    __shared__ float part[WV * ROWS];
+    if (lane % S == 0) part[wave * ROWS + r] = v;
+    __syncthreads();
+    const int set = threadIdx.x / ROWS, q = threadIdx.x % ROWS;
+    if (set < WV / KS && row0 + (int)threadIdx.x < it.M) {
+        float s = part[set * KS * ROWS + q];
+#pragma unroll
+        for (int w = 1; w < KS; ++w)
+            s += part[(set * KS + w) * ROWS + q];
+        it.y[row0 + threadIdx.x] = s;
+    }
+}
+
+// One tile per workgroup (no tile loop: its invariants would cost registers).
+template <int BITS, int G, int R, int KS, int WV>
+__global__ __launch_bounds__(WV *kWave) void k_sweep_quant_split(const DevItem *__restrict__ items,
+                                                                  const DevTile *__restrict__ tiles)
+{
+    __shared__ f4 lds[WV * SplitRows<BITS, G, R>::CH / 4];
+    const DevTile tl = tiles[blockIdx.x];
+    const DevItem it = items[tl.item];
+    tile_split<BITS, G, R, KS, WV>(it, tl.row0, lds);
+}
+
+template <int BITS, int G, int R, int KS, int WV>
+__global__ __launch_bounds__(WV *kWave) void k_item_quant_split(const DevItem it)
+{
+    __shared__ f4 lds[WV * SplitRows<BITS, G, R>::CH / 4];
+    tile_split<BITS, G, R, KS, WV>(it, (int)blockIdx.x * (R * (kWave / G) * (WV / KS)), lds);
+}
+
+template <int BITS, int G, int KS, int WV>
+struct InstSplit {
+    static constexpr int R = 4;
+    static hipError_t sweep(const DevItem *items, const DevTile *tiles, int ntiles, hipStream_t st)
+    {
+        hipLaunchKernelGGL((k_sweep_quant_split<BITS, G, R, KS, WV>), dim3(ntiles),
+                           dim3(WV * kWave), 0, st, items, tiles);
+        return hipGetLastError();
+    }
+    static hipError_t item(const DevItem &it, hipStream_t st)
+    {
+        const int rows = R * (kWave / G) * (WV / KS);
+        hipLaunchKernelGGL((k_item_quant_split<BITS, G, R, KS, WV>), dim3((it.M + rows - 1) / rows),
+                           dim3(WV * kWave), 0, st, it);
+        return hipGetLastError();
+    }
+};
+
+}  // namespace
+
+// (bits, lanes per row, wavefronts per row set, wavefronts per workgroup)
+#define TVL_SPLIT_SHAPES(X)                                                                       \
+    X(8, 16, 2, 4) X(8, 16, 4, 4) X(8, 32, 4, 4) X(8, 64, 4, 4) X(4, 8, 2, 2) X(4, 8, 4, 4)       \
+    X(4, 16, 4, 4) X(4, 32, 4, 4) X(4, 64, 4, 4)
+
+hipError_t launch_sweep_quant_split(const QuantSplit &s, const DevItem *items,
+                                    const DevTile *tiles, int ntiles, hipStream_t st)
+{
+#define X(B_, G_, K_, W_)                                                                         \
+    if (s.bits == B_ && s.lanes == G_ && s.split == K_ && s.waves == W_)                           \
+        return InstSplit<B_, G_, K_, W_>::sweep(items, tiles, ntiles, st);
+    TVL_SPLIT_SHAPES(X)
+#undef X
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_item_quant_split(const QuantSplit &s, const DevItem &item, hipStream_t st)
+{
+#define X(B_, G_, K_, W_)                                                                         \
+    if (s.bits == B_ && s.lanes == G_ && s.split == K_ && s.waves == W_)                           \
+        return InstSplit<B_, G_, K_, W_>::item(item, st);
+    TVL_SPLIT_SHAPES(X)
+#undef X
+    return hipErrorInvalidValue;
+}
+
+}  // namespace tvl

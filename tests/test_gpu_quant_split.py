@@ -1,0 +1,102 @@
+"""GPU parity of the column-split quantised kernels, the default for launches
+whose items all hold codes of one width: every configuration the rule can
+choose, at rows and columns that leave remainders in each of its splits,
+against the oracle and, on exact integer data, bit for bit against the
+whole-row kernels that an explicit tuning selects.
+
+Tolerance as for the other quantised kernels: 1e-5 of sum_j |w_ij x_j|.
+"""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_2601_03324_amd import tvl  # noqa: E402
+
+TOL = 1e-5
+# (dtype, M, K, rows per tile): the rows per tile tell which configuration the
+# plan took (8-bit: 32 rows = 16 lanes x 2 wavefronts per set, 16 / 8 / 4 = 16 /
+# 32 / 64 lanes x 4; 4-bit: 32 = 8 lanes x 2 (many rows) or x 4, 16 / 8 / 4 = 16
+# / 32 / 64 lanes x 4)
+CASES = [
+    (tvl.TVL_Q8, 24579, 77, 32), (tvl.TVL_Q8, 24577, 1031, 32),
+    (tvl.TVL_Q8, 1, 1, 16), (tvl.TVL_Q8, 19, 1023, 16), (tvl.TVL_Q8, 33, 1025, 16),
+    (tvl.TVL_Q8, 67, 2049, 8), (tvl.TVL_Q8, 9, 3969, 8),
+    (tvl.TVL_Q8, 6, 4100, 4), (tvl.TVL_Q8, 13, 28671, 4),
+    (tvl.TVL_Q4, 49155, 65, 32), (tvl.TVL_Q4, 49153, 513, 32),
+    (tvl.TVL_Q4, 1, 1, 32), (tvl.TVL_Q4, 37, 1023, 32), (tvl.TVL_Q4, 66, 1601, 32),
+    (tvl.TVL_Q4, 18, 2049, 16), (tvl.TVL_Q4, 35, 3967, 16),
+    (tvl.TVL_Q4, 10, 4097, 8), (tvl.TVL_Q4, 7, 8193, 4), (tvl.TVL_Q4, 5, 28671, 4),
+]
+
+
+def matrix(dt, M, K, seed):
+    """Codes over their whole range, scales 1/4 .. 1 (powers of two), NaN in
+    the scale plane's padding rows and junk in the codes' padding."""
+    bits = 8 if dt == tvl.TVL_Q8 else 4
+    rng = np.random.default_rng(seed)
+    ldw, ng, Mp = tvl.tvl_row_stride(K, dt) + 128, (K + 63) // 64, (M + 3) // 4 * 4
+    codes = rng.integers(0, 256, (M, ldw)).astype(np.uint8)
+    plane = np.full((Mp, ng), np.float32("nan"))
+    plane[:M] = np.exp2(rng.integers(-2, 1, (M, ng)))
+    plane = np.ascontiguousarray(plane.reshape(Mp // 4, 4, ng).transpose(0, 2, 1))
+    return np.concatenate([codes.reshape(-1), plane.reshape(-1).view(np.uint8)]), ldw, bits
+
+
+@pytest.mark.parametrize("dt,M,K,rows", CASES, ids=[f"q{8 if d == 2 else 4}-{m}x{k}"
+                                                    for d, m, k, _ in CASES])
+def test_split_configurations(dt, M, K, rows):
+    print(f"quant split {M}x{K} dtype={dt}", flush=True)
+    Wq, ldw, bits = matrix(dt, M, K, M * 31 + K)
+    Wd = tvl.upload_quant(Wq, M, K, dt, ldw)
+    rng = np.random.default_rng(K)
+    # x ends the allocation at K floats rounded up to 16 bytes: what follows is not x
+    for x, exact in ((rng.integers(-3, 4, K).astype(np.float32), True),
+                     (rng.standard_normal(K).astype(np.float32), False)):
+        xd = torch.full(((K + 3) // 4 * 4,), float("nan"), device="cuda")
+        xd[:K] = torch.from_numpy(x)
+        y = torch.full((M,), float("nan"), device="cuda")
+        plan = tvl.tvl_sweep_plan_create([(Wd.buf, ldw, xd, y, M, K, dt)])
+        assert plan.info()["rows_per_tile"] == rows
+        plan.run()
+        one = torch.full((M + 8,), float("nan"), device="cuda")
+        tvl.tvl_gemv(Wd.buf, ldw, dt, xd, one, M, K)
+        old = torch.full((M,), float("nan"), device="cuda")
+        tvl.tvl_gemv_ex(Wd.buf, ldw, dt, xd, old, M, K,
+                        dict(rows_per_wave=4, waves_per_block=4, unroll=1, flags=2))
+        torch.cuda.synchronize()
+        assert torch.equal(y, one[:M])  # a plan of one item is the single call
+        assert bool(torch.isnan(one[M:]).all())
+        if exact:  # |sums| below 2^24 quarters: no order of summation rounds
+            assert torch.equal(y, old)
+        yref, S = oracle.gemv_q(Wq, bits, ldw, M, K, x)
+        r = oracle.check(y.cpu().numpy(), yref, S, TOL)
+        assert r["bad"] == 0, r
+
+
+@pytest.mark.parametrize("dt", [tvl.TVL_Q8, tvl.TVL_Q4], ids=["q8", "q4"])
+def test_split_plan_of_ragged_items(dt):
+    """Items of different sizes share one configuration."""
+    bits = 8 if dt == tvl.TVL_Q8 else 4
+    items, keep = [], []
+    for i, (M, K) in enumerate(((1, 1), (130, 768), (17, 2777), (257, 640), (3, 5000), (64, 65))):
+        Wq, ldw, _ = matrix(dt, M, K, 7 * i + dt)
+        x = np.random.default_rng(i).standard_normal(K).astype(np.float32)
+        Wd, xd = tvl.upload_quant(Wq, M, K, dt, ldw), torch.from_numpy(x).cuda()
+        y = torch.full((M,), float("nan"), device="cuda")
+        items.append((Wd.buf, ldw, xd, y, M, K, dt))
+        keep.append((Wq, Wd, x, xd, y))
+    tvl.tvl_sweep_plan_create(items).run()
+    torch.cuda.synchronize()
+    for (W, ldw, _, y, M, K, _), (Wq, _, x, _, _) in zip(items, keep):
+        yref, S = oracle.gemv_q(Wq, bits, ldw, M, K, x)
+        r = oracle.check(y.cpu().numpy(), yref, S, TOL)
+        assert r["bad"] == 0, (M, K, r)
