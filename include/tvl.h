@@ -137,10 +137,15 @@ typedef enum tvl_status {
  *   Several vectors (nrhs > 1; beam search with nrhs hypotheses, Sec. 9.1):
  *     y[b*ldy + i] = sum_j W[i*ldw + j] * x[b*ldx + j] for b < nrhs <= 16;
  *     the weights are read once for all vectors.  Only for plain GEMV items
- *     (op == TVL_OP_GEMV, g == NULL).  Up to 4 vectors the products run on
- *     the vector ALUs, from 5 on (by default) on the matrix cores, in fp32
- *     with fp32 accumulation either way; except that launches holding only
- *     fp16 weights use the fp16 matrix cores from 5 vectors on (by default):
+ *     (op == TVL_OP_GEMV, g == NULL).  By default, launches of one weight
+ *     dtype have the wavefronts of a workgroup share 4, 8 or 16 rows and split
+ *     their columns, with fp32 products and sums on the fp32 matrix cores
+ *     (|error| <= (min(64, K/16) + K/1024 + 16) * 2^-24 sum_j |W_ij x_j|).
+ *     Long launches (many rows as long as the longest), mixed ones, and rows
+ *     above 32 MB or ldx above 2^24 give each wavefront whole rows: up to 4
+ *     vectors on the vector ALUs, from 5 on on the matrix cores, in fp32
+ *     with fp32 accumulation either way; except that such launches holding
+ *     only fp16 weights use the fp16 matrix cores from 5 vectors on:
  *     each 64- or 128-column chunk of each x vector is scaled by 2^k, which
  *     puts its largest |x| 2^k in [2^13, 2^14), and split into two fp16 parts,
  *     x 2^k = hi + lo + r with |r| <= 2^-22 |x 2^k| + 2^-25; the fp16 products
@@ -337,7 +342,8 @@ TVL_API tvl_status tvl_gemv_batch_sweep(const tvl_item *items, int32_t n,
 
 /* Sweep plan: validate `items`, build the tile table (tiles of R*W output
  * rows; R/2*W for SwiGLU items; R*W*64/G for quantised items whose rows use
- * G lanes each, and 4 to 32 rows where they split the columns; ordered by bytes per tile, largest first; in plans with
+ * G lanes each; 4 to 32 rows where quantised or several-vector items split
+ * the columns; ordered by bytes per tile, largest first; in plans with
  * several-vector or quantised items, each item's tiles are kept on as few
  * of the GPU's XCDs as the largest-first order allows, so each XCD's L2
  * fetches fewer x vectors) and upload it once.  The item

@@ -33,6 +33,7 @@ struct tvl_plan {
     bool quant = false; // some item has block-quantised weights
     int qxbytes = 0;    // quantised plan with x in LDS: dynamic LDS per workgroup
     tvl::QuantSplit qsplit; // waves > 0: the column-split quantised kernels
+    tvl::MultiSplitShape msplit; // waves > 0: the column-split several-vector kernels
     Shape shape{4, 4, 2, tvl::kXLds};
     int ks_cap = 0;
     int ntiles = 0;
@@ -477,6 +478,94 @@ tvl::QuantSplit quant_split(const tvl_item *items, int32_t n, int cus)
     return s;
 }
 
+// Several-vector launches of one weight dtype take the column split
+// (tvl_multi_split.hip) unless a tuning says otherwise or they are long enough
+// for the whole-row forms (default_multi_shape) to fill the GPU.  `wide` is the
+// rows the launch would have if all were as long as its longest, kmean the
+// columns of its mean weight.  Measured on MI355X (us, split / whole rows):
+//   - Where the whole-row forms stay: they read x once per 64 rows, the split
+//     once per 16, but a wavefront takes whole rows, 5 to 9 ns per column, so
+//     they need many rows as long as the longest.  5-16 vectors over fp16
+//     weights (4 bytes of x per vector against 2 of weights): wide >= 96 rows per
+//     CU, 9-16: 32 (8 vectors: 32000 x 768 12.4 / 10.1, 16000 x 4096 27.0 /
+//     26.4; 16: 11008 x 4096 33 / 24, 4096 x 11008 28 / 61).  fp32: 9-16 vectors 40
+//     (15955 x 6605 80 / 69, 5845 x 1979 13 / 18); 5-8, 96 and short rows (110M token
+//     72 / 70, 70B-shaped layer 513 / 551), or 48 and a last round of tiles
+//     that leaves a sixth of the time unused (13185 x 7405 74 / 67, 10752 x
+//     2954 25 / 30); 1-2, short rows and 16 (6000 x 3000 13.7 / 12.6, 11008 x 4096
+//     30 / 35; below 640 columns 8: 2816 x 301 2.9 / 2.65); 3-4 and fp16 up to 4
+//     vectors: nowhere (fp16, 4: 110M token 40 / 49, 70B-shaped layer 256 / 288).
+//   - Rows per tile: a CU takes in lines at a fixed rate once ~48 KB are in
+//     flight, so the tile height is the one whose fullest CU has the least to
+//     take in, weights and x, at the rate its wavefronts reach: 16 rows read x
+//     least often, 8 and 4 spread few rows over more CUs or even out the last
+//     round (fp32, 4 vectors, 16 / 8 / 4 rows: 1024 x 8192 13.3 / 11.4 / 7.5,
+//     2048 x 2048 5.5 / 5.0 / 4.1, 4096 x 4096 12.3 / 11.6 / 12.7, 6000 x 3000
+//     15.5 / 15.1 / 16.2, 4096 x 11008 31.2 / 33.1 / 33.8; fp16, 8: 2048 x 2048
+//     5.1 / 4.0 / 5.4).  Not 4 where a row has fewer chunks than the 8 wavefronts
+//     (768 x 768 fp16, 8: 2.9 with 8 against 3.2).
+//   - Wavefronts: 8, but in launches of many short rows fewer, which leaves
+//     each some chunks (lines of 128 bytes) to take in turn: 4 below 48 chunks
+//     per row and from 32 rows per CU (32000 x 768 fp32, 4: 16.4 against 17.9), 2 below 16 (20000 x 300:
+//     5.1 against 5.8 and 7.8; 6000 x 300 still 4: 3.5 against 3.8 and 3.8).
+tvl::MultiSplitShape multi_split(const tvl_item *items, int32_t n, int cus)
+{
+    const tvl::MultiSplitShape none;
+    tvl::MultiSplitShape s;
+    int nmax = 1;
+    double rows = 0, cells = 0, kcells = 0, kmax = 1;
+    for (int32_t i = 0; i < n; ++i) {
+        const tvl_item &t = items[i];
+        if (t.dtype != items[0].dtype) return none;
+        // the kernels address a row tile and the vectors with 32-bit offsets
+        if (t.ldw * elem_size(t.dtype) > (int64_t(1) << 25)) return none;
+        if (nvec(t) > 1 && t.ldx > (int64_t(1) << 24)) return none;
+        nmax = std::max<int>(nmax, (int)nvec(t));
+        const double c = (double)t.M * (double)t.K;
+        rows += (double)t.M;
+        cells += c;
+        kcells += c * (double)t.K;
+        kmax = std::max(kmax, (double)t.K);
+    }
+    if (n < 1) return none;
+    s.f16 = items[0].dtype == TVL_F16;
+    s.groups = nmax <= 4 ? 1 : nmax <= 8 ? 2 : 4;
+    const double wide = cells / kmax, kmean = kcells / cells;
+    if (s.f16 && s.groups > 1 && wide >= (s.groups == 4 ? 32.0 : 96.0) * cus) return none;
+    if (!s.f16 && nmax <= 2 &&
+        ((kmean < 4096.0 && wide >= 16.0 * cus) || (kmean < 640.0 && wide >= 8.0 * cus)))
+        return none;
+    if (!s.f16 && s.groups == 2 && wide >= 96.0 * cus && kmean < 4096.0) return none;
+    if (!s.f16 && s.groups == 4 && wide >= 40.0 * cus) return none;
+    const int es = elem_size(items[0].dtype);
+    double best = 0, even = 1; // of the tile chosen: cost, tiles per place in the last round
+    for (int r = 16; r >= (kmean * es < 2048.0 ? 8 : 4); r /= 2) {
+        int64_t tiles = 0;
+        for (int32_t i = 0; i < n; ++i)
+            tiles += (items[i].M + r - 1) / r;
+        const double each = (double)((tiles + cus - 1) / cus); // tiles of the fullest CU
+        const int line = r == 4 ? 256 : 128;                   // a chunk: bytes per row
+        const double flight = each * 16 * (r * line + nmax * 4 * line / es);
+        const double cost = each * (r * es + 4 * nmax) / std::min(1.0, flight / 49152.0) *
+                            (r == 8 ? 0.98 : 1.0); // (equal where both are short of loads in flight: 8)
+        if (s.rows == 0 || cost < best) {
+            best = cost;
+            even = (double)tiles / (each * cus);
+            s.rows = r;
+        }
+    }
+    if (!s.f16 && s.groups == 2 && wide >= 48.0 * cus && even < 0.85) return none;
+    s.waves = 8;
+    const double chunks = kmean * es / 128.0;
+    if (s.rows == 16 && chunks < 16.0)
+        s.waves = rows >= 64.0 * cus ? 2 : 4;
+    else if (s.rows == 16 && chunks < 48.0 && rows >= 32.0 * cus)
+        s.waves = 4;
+    // a launch holds less than 2^32 threads
+    if ((rows / s.rows + n) * s.waves * 64 >= 4294967296.0) return none;
+    return s;
+}
+
 // A tuning that chooses the kernel: any field but ksplit, which only says
 // that there is none.
 bool tunes(const tvl_tuning *t)
@@ -732,6 +821,7 @@ tvl_status plan_build(const tvl_item *items, int32_t n, const tvl_tuning *tuning
     p->multiB = multiB;
     p->wmode = f32 && f16 ? 2 : f16 ? 1 : 0;
     if (quant && !tunes(tuning)) p->qsplit = quant_split(items, n, info.cus);
+    if (multiB && !tunes(tuning)) p->msplit = multi_split(items, n, info.cus);
     // output rows per tile: a SwiGLU tile streams R rows of W and of W3 per
     // wavefront, i.e. R/2 output rows; a quantised item whose rows share a
     // wavefront in groups of G lanes covers 64 / G times R rows per wavefront
@@ -747,6 +837,7 @@ tvl_status plan_build(const tvl_item *items, int32_t n, const tvl_tuning *tuning
     };
     auto rows_of = [&](const tvl_item &t) {
         if (p->qsplit.waves) return p->qsplit.rows();
+        if (p->msplit.waves) return p->msplit.rows;
         return (t.op == TVL_OP_SWIGLU ? shape.R / 2 : shape.R) * shape.W * (64 / lanes_of(t));
     };
     // bytes per tile, largest first, so the longest tiles start first
@@ -817,6 +908,8 @@ tvl_status plan_launch(const tvl_plan *p, hipStream_t st)
     const hipError_t e =
         p->qsplit.waves ? tvl::launch_sweep_quant_split(p->qsplit, p->d_items, p->d_tiles,
                                                         p->ntiles, st)
+        : p->msplit.waves ? tvl::launch_sweep_multi_split(p->msplit, p->d_items, p->d_tiles,
+                                                          p->ntiles, st)
         : p->quant  ? tvl::launch_sweep_quant(p->shape, p->d_items, p->d_tiles, p->ntiles, p->grid,
                                               p->qxbytes, st)
         : p->multiB ? tvl::launch_sweep_multi(p->shape, p->multiB, p->wmode, p->d_items,
@@ -1068,8 +1161,11 @@ tvl_status tvl_gemv_item(const tvl_item *item, const tvl_tuning *tuning, hipStre
     st = current_device(&dev, &info);
     if (st != TVL_OK) return st;
     const DevItem d = dev_item(*item);
-    const hipError_t e =
-        B ? tvl::launch_item_multi(shape, B, d, stream) : tvl::launch_item(shape, d, stream);
+    tvl::MultiSplitShape ms;
+    if (B && !tunes(tuning)) ms = multi_split(item, 1, info.cus);
+    const hipError_t e = ms.waves ? tvl::launch_item_multi_split(ms, d, stream)
+                         : B      ? tvl::launch_item_multi(shape, B, d, stream)
+                                  : tvl::launch_item(shape, d, stream);
     if (e != hipSuccess) return fail_hip(e, "item launch");
     return TVL_OK;
 }
@@ -1107,7 +1203,9 @@ tvl_status tvl_sweep_plan_info(const tvl_plan *plan, int64_t *ntiles, int64_t *g
     if (ntiles) *ntiles = plan->ntiles;
     if (grid) *grid = plan->grid;
     if (rows_per_tile)
-        *rows_per_tile = plan->qsplit.waves ? plan->qsplit.rows() : plan->shape.R * plan->shape.W;
+        *rows_per_tile = plan->qsplit.waves   ? plan->qsplit.rows()
+                         : plan->msplit.waves ? plan->msplit.rows
+                                              : plan->shape.R * plan->shape.W;
     return TVL_OK;
 }
 

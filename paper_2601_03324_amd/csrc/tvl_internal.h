@@ -166,6 +166,19 @@ hipError_t launch_sweep_multi(const Shape &s, int B, int wmode, const DevItem *i
                               const DevTile *tiles, int ntiles, int grid, hipStream_t st);
 hipError_t launch_item_multi(const Shape &s, int B, const DevItem &item, hipStream_t st);
 
+// Several-vector launches of one weight dtype whose workgroups' `waves`
+// wavefronts split the columns of each `rows` rows (4, 8 or 16), up to
+// 4 * groups vectors.  A launch without the split has waves == 0.
+struct MultiSplitShape {
+    bool f16 = false;
+    int groups = 0;
+    int rows = 0; // per tile
+    int waves = 0;
+};
+hipError_t launch_sweep_multi_split(const MultiSplitShape &s, const DevItem *items,
+                                    const DevTile *tiles, int ntiles, hipStream_t st);
+hipError_t launch_item_multi_split(const MultiSplitShape &s, const DevItem &item, hipStream_t st);
+
 hipError_t launch_pack(int dtype, void *dst, int64_t ldw, const void *src, int64_t M,
                        int64_t K, hipStream_t st);
 

@@ -1,0 +1,371 @@
+// tvl_multi_split.hip -- several-vector GEMV (beam search) over fp32 or fp16
+// weights: the wavefronts of a workgroup share 4, 8 or 16 rows and split their
+// columns; products on the fp32 matrix cores.  The default for launches of one
+// weight dtype unless they are long ones (multi_split in tvl_abi.cpp says when
+// it takes which configuration, and why).
+//
+// What bounds it: a launch of few rows, the dependent rounds of its wavefronts
+// and the CUs it reaches; a launch of many, the rate at which a CU takes in
+// lines (~56 GB/s here, measured with 19 to 64 workgroups whatever is in
+// flight, loads into LDS or into registers alike), which x shares with the
+// weights: (4 or 2) R bytes of weights and 4 nrhs of x per column of an R-row
+// tile.  With whole rows per wavefront a 4096 x 4096 matrix filled 64 of 256
+// CUs (16 rows x 4 wavefronts) and 1024 x 8192 16; with the columns split over
+// 8 wavefronts they fill 256.  So R is the largest of 16, 8 and 4 that still
+// gives every CU a workgroup.
+//
+// Per chunk of columns a wavefront loads its rows' 128 (or 256) bytes and the
+// vectors' columns straight into LDS (1 KiB per load, whole lines; the rows are
+// transposed by the LDS reads), two chunks per wavefront in flight and up to
+// 24 wavefronts per CU, no barrier before the last sum.  The 4 x 4 x 1 matrix
+// instruction does 16 blocks of 4 rows x 4 vectors, so up to 4 vectors cost a
+// quarter of the 16 x 16 x 4 form and nothing is split or rounded: products
+// and sums are fp32, as on the vector ALUs.
+//
+// Measured (us, against the whole-row forms): 4096 x 4096 fp16, 4 vectors 11.6
+// -> 6.8; 8 vectors 24.3 -> 7.9; 1024 x 8192 fp32, 4 vectors 28.6 -> 7.5; 8:
+// 55.2 -> 8.5; 4000 x 28672 fp16, 8: 152 -> 48 (4.8 TB/s); one 110M layer fp32,
+// 8: 15.8 -> 8.4; one 4096-wide layer fp32, 4: 130 -> 122 (6.6 TB/s).
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "tvl_device.h"
+
+namespace tvl {
+namespace {
+
+#define TVL_LDS __attribute__((address_space(3)))
+
+// 4 x 4 outer products of 16 independent blocks: lane l = 4 b + q supplies row
+// q of A_b and column q of B_b and holds column q of D_b, row v in element v.
+__device__ __forceinline__ f4 mfma4(float a, float b, f4 c)
+{
+    return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const void *base, int64_t bytes)
+{
+    const int n = bytes > 0x7fffffff ? 0x7fffffff : (int)bytes;
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, n, 0x00020000);
+}
+
+// 4 RB NW rows of W and 4 P vectors.  A chunk is LB bytes of every row (CC
+// columns) and the vectors' CC columns.  Block b of the matrix-core
+// instruction takes piece b % LP (16 bytes, N columns) of rows 4 (b / LP) ..
+// + 3 of each group of 4 RB rows.
+template <typename T, int P, int RB, int NW, int S>
+struct MultiSplit {
+    static constexpr int ES = (int)sizeof(T);
+    static constexpr int N = 16 / ES;                     // columns per piece
+    static constexpr int LP = 16 / RB;                    // pieces of a row's chunk
+    static constexpr int LB = 16 * LP;                    // bytes of it: 128 or 256
+    static constexpr int CC = LB / ES;                    // columns per chunk
+    static constexpr int ROWS = 4 * RB * NW;
+    static constexpr int XROW = 4 * CC;                   // bytes of a vector's chunk
+    static constexpr int XP = XROW / 16;                  // 16-byte pieces of it
+    static constexpr int NX = N / 4;                      // x pieces per weight piece
+    static constexpr int VPL = kWave / XP;                // vectors per load
+    static constexpr int NXL = (4 * P + VPL - 1) / VPL;   // x loads per chunk
+    static constexpr int L = NW + NXL;                    // with NW weight loads of 4 RB rows
+    static constexpr int STAGE = 1024 * L;
+    static constexpr int kFlush = 16 / N;                 // chunks between flushes: 64 products
+    static constexpr int kNone = (int)0x80000000u;        // past any descriptor's end
+    static_assert(RB == 1 || RB == 2, "a chunk is one or two lines of a row");
+    static_assert((S - 1) * L < 64, "vmcnt range");
+
+    __amdgpu_buffer_rsrc_t wr, xr;
+    int vw[NW], vx[NXL], xcol[NXL], wcol, K, lane;
+    TVL_LDS char *lds; // this wavefront's stages
+
+    // swizzle of 16-byte pieces: the 16 lanes that read four pieces of four
+    // rows (or vectors) touch the 16 positions of a 256-byte LDS line
+    static __device__ __forceinline__ int swz(int bytes, int r)
+    {
+        return bytes == 128 ? 4 * ((r >> 1) & 1) : 4 * (r & 3);
+    }
+    static __device__ __forceinline__ int swz_w(int r) { return swz(LB, r); }
+    static __device__ __forceinline__ int swz_x(int v) // two pieces apart with fp16 weights
+    {
+        return NX == 1 ? swz(XROW, v) : (v & 1) | (((v >> 1) & 1) << 3);
+    }
+
+    __device__ __forceinline__ MultiSplit(const DevItem &it, int row0, int lane_, TVL_LDS char *lds_)
+        : K(it.K), lane(lane_), lds(lds_)
+    {
+        const int left = min(it.M - row0, ROWS);
+        const int nb = it.nrhs < 1 ? 1 : it.nrhs;
+        const int64_t pitch = it.ldw * ES;
+        wr = rsrc_of(static_cast<const char *>(it.W) + (int64_t)row0 * pitch, left * pitch);
+        xr = rsrc_of(it.x, 4 * ((nb - 1) * it.ldx + (((int64_t)it.K + 3) & ~(int64_t)3)));
+        const int piece = (lane % LP) ^ swz_w(lane / LP);
+        wcol = N * piece;
+#pragma unroll
+        for (int i = 0; i < NW; ++i) // rows past M repeat row M - 1 (not stored)
+            vw[i] = (int)(min(4 * RB * i + lane / LP, left - 1) * pitch) + 16 * piece;
+#pragma unroll
+        for (int i = 0; i < NXL; ++i) { // vectors past nb are not read (columns of no output)
+            const int v = VPL * i + lane / XP;
+            const int col = 4 * ((lane % XP) ^ swz_x(v));
+            vx[i] = (int)(4 * min(v, nb - 1) * it.ldx) + 4 * col;
+            xcol[i] = v < nb ? col : (1 << 30);
+        }
+    }
+
+    // Loads of chunk c into stage s, or L loads of nothing (past the row's
+    // last chunk); no 16-byte piece past the row's last one is read.
+    __device__ __forceinline__ void issue(int c, int nc, int s) const
+    {
+        TVL_LDS char *st = lds + s * STAGE;
+        const int cols = c < nc ? K - c * CC : 0;
+#pragma unroll
+        for (int i = 0; i < NW; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, (TVL_LDS void *)(st + 1024 * i), 16,
+                                                     wcol < cols ? vw[i] + c * LB : kNone, 0, 0, 2);
+#pragma unroll
+        for (int i = 0; i < NXL; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                xr, (TVL_LDS void *)(st + 1024 * (NW + i)), 16,
+                xcol[i] < cols ? vx[i] + c * XROW : kNone, 0, 0, 0);
+    }
+
+    struct Chunk {
+        f4 w[NW];
+        f4 x[P][NX];
+    };
+
+    __device__ __forceinline__ void read(int s, Chunk &t) const
+    {
+        const int q = lane & 3, k = (lane >> 2) % LP, hi = (lane >> 2) / LP;
+        const TVL_LDS char *st = lds + s * STAGE;
+        const TVL_LDS char *a = st + (4 * hi + q) * LB + 16 * (k ^ swz_w(q));
+#pragma unroll
+        for (int i = 0; i < NW; ++i)
+            t.w[i] = *(const TVL_LDS f4 *)(a + 1024 * i);
+#pragma unroll
+        for (int h = 0; h < NX; ++h) {
+            const TVL_LDS char *b = st + 1024 * NW + q * XROW + 16 * ((NX * k + h) ^ swz_x(q));
+#pragma unroll
+            for (int p = 0; p < P; ++p)
+                t.x[p][h] = *(const TVL_LDS f4 *)(b + 4 * p * XROW);
+        }
+    }
+
+    __device__ __forceinline__ void mask(int c, Chunk &t) const
+    {
+        const int valid = K - c * CC - N * ((lane >> 2) % LP); // of the lane's piece
+        using V = typename Vec<T>::type;
+#pragma unroll
+        for (int i = 0; i < NW; ++i)
+            t.w[i] = __builtin_bit_cast(f4, mask_from<V, N>(__builtin_bit_cast(V, t.w[i]), valid));
+#pragma unroll
+        for (int p = 0; p < P; ++p)
+#pragma unroll
+            for (int h = 0; h < NX; ++h)
+                t.x[p][h] = mask_from<f4, 4>(t.x[p][h], valid - 4 * h);
+    }
+
+    __device__ __forceinline__ void multiply(const Chunk &t, f4 (&acc)[NW][P]) const
+    {
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+            float wf[N];
+            if constexpr (N == 4) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    wf[e] = t.w[i][e];
+            } else {
+                const f8 c = __builtin_convertvector(__builtin_bit_cast(h8, t.w[i]), f8);
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    wf[e] = c[e];
+            }
+#pragma unroll
+            for (int e = 0; e < N; ++e)
+#pragma unroll
+                for (int p = 0; p < P; ++p)
+                    acc[i][p] = mfma4(wf[e], t.x[p][e / 4][e % 4], acc[i][p]);
+        }
+    }
+
+    // chunks c0, c0 + step, ...
+    __device__ __forceinline__ void run(int c0, int step, f4 (&tot)[NW][P]) const
+    {
+        const f4 z = {0.f, 0.f, 0.f, 0.f};
+        const int nc = (K + CC - 1) / CC;
+        f4 acc[NW][P];
+#pragma unroll
+        for (int i = 0; i < NW; ++i)
+#pragma unroll
+            for (int p = 0; p < P; ++p)
+                tot[i][p] = acc[i][p] = z;
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+            issue(c0 + s * step, nc, s);
+        int s = 0, n = 0;
+        constexpr int W = (S - 1) * L;
+        for (int c = c0; c < nc; c += step) {
+            // the oldest chunk has landed; S - 1 stay in flight
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_waitcnt((W & 15) | ((W >> 4) << 14) | 0x0F70);
+            __builtin_amdgcn_sched_barrier(0);
+            Chunk t;
+            read(s, t);
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_waitcnt(0xC07F); // lgkmcnt(0): the stage is read
+            __builtin_amdgcn_sched_barrier(0);
+            issue(c + S * step, nc, s);
+            __builtin_amdgcn_sched_barrier(0);
+            if ((c + 1) * CC > K) mask(c, t); // wavefront-uniform
+            multiply(t, acc);
+            if (++n == kFlush) {
+                n = 0;
+#pragma unroll
+                for (int i = 0; i < NW; ++i)
+#pragma unroll
+                    for (int p = 0; p < P; ++p) {
+                        tot[i][p] += acc[i][p];
+                        acc[i][p] = z;
+                    }
+            }
+            s = s + 1 == S ? 0 : s + 1;
+        }
+#pragma unroll
+        for (int i = 0; i < NW; ++i)
+#pragma unroll
+            for (int p = 0; p < P; ++p)
+                tot[i][p] += acc[i][p];
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0x0F70); // the empty loads too: the stages are reused
+        __builtin_amdgcn_sched_barrier(0);
+    }
+};
+
+// Sum N values per lane over the lanes that differ in bits BIT, BIT / 2, .. 4,
+// halving the values while there are several: returns the index of the lane's
+// first value, and leaves max(1, N >> steps) values.
+template <int N, int BIT>
+__device__ __forceinline__ int sum_pieces(float *v, int lane)
+{
+    if constexpr (BIT < 4) {
+        return 0;
+    } else if constexpr (N > 1) {
+        halve<N / 2, BIT>(v, lane);
+        return (lane & BIT ? N / 2 : 0) + sum_pieces<N / 2, BIT / 2>(v, lane);
+    } else {
+        v[0] += __shfl_xor(v[0], BIT);
+        return sum_pieces<N, BIT / 2>(v, lane);
+    }
+}
+
+template <typename T, int P, int RB, int NW, int S, int WV>
+__device__ __forceinline__ void tile_multi_split(const DevItem &it, int row0, f4 *lds)
+{
+    using Rows = MultiSplit<T, P, RB, NW, S>;
+    constexpr int NV = 4 * NW * P;                      // values per lane
+    constexpr int LEFT = NV * RB >= 16 ? NV * RB / 16 : 1; // after the sum over pieces
+    constexpr int ROWS = Rows::ROWS;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    TVL_LDS char *mine = (TVL_LDS char *)lds + wave * (S * Rows::STAGE);
+    f4 tot[NW][P];
+    Rows(it, row0, lane, mine).run(wave, WV, tot);
+    float v[NV];
+#pragma unroll
+    for (int i = 0; i < NW; ++i)
+#pragma unroll
+        for (int p = 0; p < P; ++p)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                v[(i * P + p) * 4 + e] = tot[i][p][e];
+    const int first = sum_pieces<NV, 32 / RB>(v, lane);
+    // value (i, p, e) of lane (hi, q): row 4 RB i + 4 hi + e, vector 4 p + q
+    const int at = (RB == 2 ? 4 * (lane >> 5) : 0) + (lane & 3);
+    TVL_LDS float *part = (TVL_LDS float *)mine;
+#pragma unroll
+    for (int i = 0; i < LEFT; ++i)
+        part[(first + i) * (4 * RB) + at] = v[i];
+    __syncthreads();
+    const TVL_LDS float *all = (const TVL_LDS float *)lds;
+    constexpr int PITCH = S * Rows::STAGE / 4;
+    static_assert(NV * 4 * RB <= PITCH, "the partial sums fit the stages");
+    const int nb = it.nrhs < 1 ? 1 : it.nrhs;
+#pragma unroll
+    for (int t0 = 0; t0 < 4 * P * ROWS; t0 += WV * kWave) {
+        const int t = t0 + (int)threadIdx.x;
+        const int r = t % ROWS, b = t / ROWS;
+        if (b < nb && row0 + r < it.M) { // (b < nb <= 4 P bounds t)
+            const int k = ((r / (4 * RB) * P + b / 4) * 4 + r % 4) * (4 * RB) +
+                          (RB == 2 ? r & 4 : 0) + b % 4;
+            float s = all[k];
+#pragma unroll
+            for (int w = 1; w < WV; ++w)
+                s += all[w * PITCH + k];
+            it.y[(int64_t)b * it.ldy + row0 + r] = s;
+        }
+    }
+}
+
+template <typename T, int P, int RB, int NW, int S, int WV>
+__global__ __launch_bounds__(WV *kWave) void k_sweep_multi_split(const DevItem *__restrict__ items,
+                                                                  const DevTile *__restrict__ tiles)
+{
+    __shared__ f4 lds[WV * S * MultiSplit<T, P, RB, NW, S>::STAGE / 16];
+    const DevTile tl = tiles[blockIdx.x];
+    const DevItem it = items[tl.item];
+    tile_multi_split<T, P, RB, NW, S, WV>(it, tl.row0, lds);
+}
+
+template <typename T, int P, int RB, int NW, int S, int WV>
+__global__ __launch_bounds__(WV *kWave) void k_item_multi_split(const DevItem it)
+{
+    __shared__ f4 lds[WV * S * MultiSplit<T, P, RB, NW, S>::STAGE / 16];
+    tile_multi_split<T, P, RB, NW, S, WV>(it, (int)blockIdx.x * (4 * RB * NW), lds);
+}
+
+template <typename T, int P, int RB, int NW, int S, int WV>
+hipError_t launch(const DevItem *items, const DevTile *tiles, int n, const DevItem *one,
+                  hipStream_t st)
+{
+    constexpr int ROWS = 4 * RB * NW;
+    if (one)
+        hipLaunchKernelGGL((k_item_multi_split<T, P, RB, NW, S, WV>),
+                           dim3((one->M + ROWS - 1) / ROWS), dim3(WV * kWave), 0, st, *one);
+    else
+        hipLaunchKernelGGL((k_sweep_multi_split<T, P, RB, NW, S, WV>), dim3(n), dim3(WV * kWave),
+                           0, st, items, tiles);
+    return hipGetLastError();
+}
+
+// (row blocks, weight loads, wavefronts): 4, 8 and 16 rows per tile
+#define TVL_MULTI_SPLIT_SHAPES(X, P) X(P, 1, 1, 8) X(P, 2, 1, 8) X(P, 2, 2, 8) X(P, 2, 2, 4) X(P, 2, 2, 2)
+
+template <typename T>
+hipError_t pick(const MultiSplitShape &s, const DevItem *items, const DevTile *tiles, int n,
+                const DevItem *one, hipStream_t st)
+{
+#define X(P_, RB_, NW_, W_)                                                                       \
+    if (s.groups == P_ && s.rows == 4 * RB_ * NW_ && s.waves == W_)                                \
+        return launch<T, P_, RB_, NW_, 2, W_>(items, tiles, n, one, st);
+    TVL_MULTI_SPLIT_SHAPES(X, 1)
+    TVL_MULTI_SPLIT_SHAPES(X, 2)
+    TVL_MULTI_SPLIT_SHAPES(X, 4)
+#undef X
+    return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+hipError_t launch_sweep_multi_split(const MultiSplitShape &s, const DevItem *items,
+                                    const DevTile *tiles, int ntiles, hipStream_t st)
+{
+    return s.f16 ? pick<_Float16>(s, items, tiles, ntiles, nullptr, st)
+                 : pick<float>(s, items, tiles, ntiles, nullptr, st);
+}
+
+hipError_t launch_item_multi_split(const MultiSplitShape &s, const DevItem &item, hipStream_t st)
+{
+    return s.f16 ? pick<_Float16>(s, nullptr, nullptr, 0, &item, st)
+                 : pick<float>(s, nullptr, nullptr, 0, &item, st);
+}
+
+}  // namespace tvl

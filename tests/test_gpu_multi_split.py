@@ -1,0 +1,142 @@
+"""GPU parity of the column-split several-vector kernels, the default for
+launches of one weight dtype that are not long: every configuration the rule
+can choose, at rows, columns and vectors that leave remainders in each of its
+splits, against the oracle and, on exact integer data, bit for bit against the
+whole-row kernels that an explicit tuning selects.
+
+Tolerance: 1e-5 of sum_j |W_ij x_j|, above the split's bound of
+(64 + K/1024 + 16) 2^-24 = 6.5e-6 at the largest K here.
+"""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_2601_03324_amd import tvl  # noqa: E402
+
+TOL = 1e-5
+DEV = "cuda"
+F32, F16 = tvl.TVL_F32, tvl.TVL_F16
+# (dtype, M, K, vectors, rows per tile).  16 rows: 2 wavefronts below 16 lines
+# per row in many rows, 4 below 48 or in fewer rows, else 8.
+CASES = [
+    (F32, 7, 2063, 4, 4), (F32, 1021, 519, 3, 4), (F32, 9, 28671, 4, 4), (F32, 6, 519, 5, 4),
+    (F32, 5, 8191, 9, 4), (F16, 5, 2111, 2, 4), (F16, 1021, 4099, 7, 4), (F16, 3, 16387, 16, 4),
+    (F32, 1, 1, 2, 8), (F32, 2557, 65, 3, 8), (F32, 1030, 1025, 8, 8), (F32, 15, 33, 16, 8),
+    (F32, 1537, 2051, 11, 8), (F16, 1, 1, 3, 8), (F16, 17, 127, 4, 8), (F16, 1543, 2050, 6, 8),
+    (F16, 769, 771, 16, 8),
+    (F32, 16399, 130, 3, 16), (F32, 12283, 700, 4, 16), (F32, 8185, 2001, 4, 16),
+    (F32, 20470, 300, 5, 16), (F32, 8205, 600, 8, 16), (F32, 4090, 513, 8, 16),
+    (F32, 10239, 31, 13, 16), (F32, 4093, 2000, 12, 16),
+    (F16, 16385, 77, 4, 16), (F16, 16401, 1100, 4, 16), (F16, 4077, 3073, 4, 16),
+    (F16, 16385, 77, 8, 16), (F16, 16385, 1500, 6, 16), (F16, 4080, 3075, 8, 16),
+    (F16, 4081, 65, 16, 16), (F16, 4080, 3075, 16, 16),
+]
+
+
+def dev_matrix(host, dt, pad):
+    """Rows of the minimal stride plus `pad` lines, NaN in the padding."""
+    M, K = host.shape
+    ldw = tvl.tvl_row_stride(K, dt) + pad * (32 if dt == F32 else 64)
+    buf = torch.full((M, ldw), float("nan"), dtype=torch.float32 if dt == F32 else torch.float16,
+                     device=DEV)
+    host = np.ascontiguousarray(host)
+    buf[:, :K] = torch.from_numpy(host if dt == F32 else host.view(np.float16)).to(DEV)
+    return buf, ldw
+
+
+def x_rows(X, gap):
+    """x rows of K floats rounded up to 16 bytes plus `gap`; the last row ends
+    the allocation at its last 16 bytes; NaN where x does not reach."""
+    n, K = X.shape
+    ldx = (K + 3) // 4 * 4 + gap
+    buf = torch.full(((n - 1) * ldx + (K + 3) // 4 * 4,), float("nan"), device=DEV)
+    for b in range(n):
+        buf[b * ldx:b * ldx + K] = torch.from_numpy(X[b]).to(DEV)
+    return buf, ldx
+
+
+@pytest.mark.parametrize("dt,M,K,n,rows", CASES,
+                         ids=[f"{'f32' if d == F32 else 'f16'}-{m}x{k}-{n}"
+                              for d, m, k, n, _ in CASES])
+def test_split_configurations(dt, M, K, n, rows):
+    print(f"multi split {M}x{K} dtype={dt} vectors={n}", flush=True)
+    rng = np.random.default_rng(M * 31 + K * 7 + n)
+    for exact in (True, False):
+        if exact:
+            Wf = rng.integers(-3, 4, (M, K)).astype(np.float32)
+            X = rng.integers(-3, 4, (n, K)).astype(np.float32)
+        else:
+            Wf = (rng.standard_normal((M, K)) * 0.02).astype(np.float32)
+            X = rng.standard_normal((n, K)).astype(np.float32)
+        W = Wf if dt == F32 else synth.f32_to_f16_bits(Wf)
+        buf, ldw = dev_matrix(W, dt, pad=1 if exact else 0)
+        xd, ldx = x_rows(X, 0 if exact else 8)
+        ldy = M + 3
+        Y = torch.full((n, ldy), -12345.0, device=DEV)
+        it = dict(W=buf, ldw=ldw, x=xd, y=Y, M=M, K=K, dtype=dt, nrhs=n, ldx=ldx, ldy=ldy)
+        plan = tvl.tvl_sweep_plan_create([it])
+        assert plan.info()["rows_per_tile"] == rows
+        plan.run()
+        one = torch.full((n, ldy), -12345.0, device=DEV)
+        tvl.tvl_gemv_item(dict(it, y=one))
+        torch.cuda.synchronize()
+        assert torch.equal(Y, one)  # a plan of one item is the single call
+        assert bool((Y[:, M:] == -12345.0).all())
+        if exact:  # |sums| below 2^24: no order of summation rounds
+            old = torch.full((n, ldy), -12345.0, device=DEV)
+            tvl.tvl_gemv_item(dict(it, y=old),
+                              dict(rows_per_wave=32, waves_per_block=1, unroll=2, flags=2))
+            torch.cuda.synchronize()
+            assert torch.equal(Y, old)
+            continue
+        got = Y[:, :M].cpu().numpy()
+        for b in range(n):
+            yref, S = (oracle.gemv_f32 if dt == F32 else oracle.gemv_f16)(W, X[b])
+            r = oracle.check(got[b], yref, S, TOL)
+            assert r["bad"] == 0, (b, r)
+
+
+# (items: M, K, vectors; rows per tile): few rows; many short ones beside a few
+# long ones (16 rows, 2 wavefronts, more than 8 vectors)
+PLANS = [
+    (((1, 1, 2), (130, 768, 5), (17, 2777, 1), (257, 640, 16), (3, 5000, 3), (64, 65, 9)), (4, 8)),
+    (((16391, 40, 11), (3, 9000, 16), (33, 41, 1)), (16,)),
+]
+
+
+@pytest.mark.parametrize("dt", [F32, F16], ids=["f32", "f16"])
+@pytest.mark.parametrize("mats,rows", PLANS, ids=["few", "many"])
+def test_split_plan_of_mixed_items(mats, rows, dt):
+    """Items of different sizes and numbers of vectors (one among them) share
+    one configuration."""
+    items, keep = [], []
+    for i, (M, K, n) in enumerate(mats):
+        rng = np.random.default_rng(7 * i + dt)
+        Wf = (rng.standard_normal((M, K)) * 0.02).astype(np.float32)
+        W = Wf if dt == F32 else synth.f32_to_f16_bits(Wf)
+        X = rng.standard_normal((n, K)).astype(np.float32)
+        buf, ldw = dev_matrix(W, dt, pad=i % 2)
+        xd, ldx = x_rows(X, 4 * i)
+        Y = torch.full((n, M), float("nan"), device=DEV)
+        items.append(dict(W=buf, ldw=ldw, x=xd, y=Y, M=M, K=K, dtype=dt, nrhs=n,
+                          ldx=ldx if n > 1 else -(1 << 40), ldy=M if n > 1 else 0))
+        keep.append((W, X, buf, xd, Y))
+    plan = tvl.tvl_sweep_plan_create(items)
+    assert plan.info()["rows_per_tile"] in rows
+    plan.run()
+    torch.cuda.synchronize()
+    for W, X, _, _, Y in keep:
+        for b in range(len(X)):
+            yref, S = (oracle.gemv_f32 if dt == F32 else oracle.gemv_f16)(W, X[b])
+            r = oracle.check(Y[b].cpu().numpy(), yref, S, TOL)
+            assert r["bad"] == 0, (W.shape, b, r)
