@@ -29,9 +29,10 @@
  *     NaN at j and 0 elsewhere, so every output is NaN.
  *   - Summation order differs from the sequential loop (Sec. 5.2 accepts the
  *     drift of reordered fused multiply-add accumulation).  Each output is
- *     the sum of 256 interleaved fp32 partial sums (64 lanes x 4) joined by
- *     a fixed tree, so |y_i - exact| <= (K/256 + 8) * 2^-24 * sum_j |W_ij x_j|
- *     up to second-order terms, and reruns of one variant are bitwise equal.
+ *     the sum of at least 256 interleaved fp32 partial sums (64 lanes x 4, of
+ *     one to four wavefronts) joined in a fixed order, so |y_i - exact| <=
+ *     (K/256 + 11) * 2^-24 * sum_j |W_ij x_j| up to second-order terms, and
+ *     reruns of one variant are bitwise equal.
  *
  * Memory and ownership.  All W, x, y pointers are device pointers owned by
  * the caller; the library never allocates, frees or retains them.  The same
@@ -276,7 +277,8 @@ TVL_API tvl_status tvl_pack_rows(void *dst, int64_t ldw, const void *src,
 
 /* y = W x (Sec. 6.1), one launch.  The library picks the variant by shape
  * (from timings on MI355X): a row split (each wavefront owns R whole rows;
- * one row per single-wavefront workgroup when M is small), or, for very few
+ * one row per single-wavefront workgroup when M is small), a column split
+ * (wavefronts of a workgroup share R rows and join their sums), or, for very few
  * long rows (M <= 128, rows >= 32 KB), a K split: S workgroups share a row
  * tile, each sums one slice of K into an fp32 partial, and the last
  * workgroup to finish adds the S partials in the fixed order 0..S-1, so
@@ -321,7 +323,8 @@ TVL_API tvl_status tvl_gemv_noalloc(const void *W, int64_t ldw, int32_t dtype,
                                     const tvl_tuning *tuning, hipStream_t stream);
 
 /* One item (any op, with or without RMSNorm) in one launch.  A plain GEMV
- * item is the same as tvl_gemv_ex; fused items use the direct-x row split.
+ * item is the same as tvl_gemv_ex; fused items use the direct-x row split or
+ * the column split.
  * `tuning` may be NULL. */
 TVL_API tvl_status tvl_gemv_item(const tvl_item *item, const tvl_tuning *tuning,
                                  hipStream_t stream);
@@ -342,8 +345,7 @@ TVL_API tvl_status tvl_gemv_batch_sweep(const tvl_item *items, int32_t n,
 
 /* Sweep plan: validate `items`, build the tile table (tiles of R*W output
  * rows; R/2*W for SwiGLU items; R*W*64/G for quantised items whose rows use
- * G lanes each; 4 to 32 rows where quantised or several-vector items split
- * the columns; ordered by bytes per tile, largest first; in plans with
+ * G lanes each; 1 to 32 rows where wavefronts split the columns; ordered by bytes per tile, largest first; in plans with
  * several-vector or quantised items, each item's tiles are kept on as few
  * of the GPU's XCDs as the largest-first order allows, so each XCD's L2
  * fetches fewer x vectors) and upload it once.  The item

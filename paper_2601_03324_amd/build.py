@@ -19,7 +19,7 @@ LIB = os.path.join(PKG, "libtvl.so")
 ARCH = "gfx950"
 # one translation unit per kernel family, plus the C-ABI layer
 SOURCES = ["tvl_gemv.hip", "tvl_fused.hip", "tvl_multi.hip", "tvl_multi_split.hip",
-           "tvl_quant.hip", "tvl_quant_split.hip", "tvl_util.hip", "tvl_abi.cpp"]
+           "tvl_quant.hip", "tvl_quant_split.hip", "tvl_rows_split.hip", "tvl_util.hip", "tvl_abi.cpp"]
 OBJDIR = os.path.join(PKG, "_build")
 FLAGS = [
     f"--offload-arch={ARCH}",

@@ -33,6 +33,7 @@ struct tvl_plan {
     bool quant = false; // some item has block-quantised weights
     int qxbytes = 0;    // quantised plan with x in LDS: dynamic LDS per workgroup
     tvl::QuantSplit qsplit; // waves > 0: the column-split quantised kernels
+    tvl::RowsSplit rsplit;       // waves > 0: the column-split one-vector kernels
     tvl::MultiSplitShape msplit; // waves > 0: the column-split several-vector kernels
     Shape shape{4, 4, 2, tvl::kXLds};
     int ks_cap = 0;
@@ -566,6 +567,119 @@ tvl::MultiSplitShape multi_split(const tvl_item *items, int32_t n, int cus)
     return s;
 }
 
+// One-vector launches of one weight dtype take the column split
+// (tvl_rows_split.hip) unless a tuning says otherwise or the whole-row forms
+// are as fast.  set x split / waves below: weight rows per set, wavefronts that
+// share it, wavefronts per workgroup; rows: weight rows of the launch (a SwiGLU
+// pair has two per output); kmean: the columns of its mean weight.  Measured on
+// MI355X (us, split / whole rows):
+//   - fp32.  A whole-row wavefront takes a row of up to 768 columns in one round:
+//     it stays below 8 rows per CU (1763 x 768 2.45 / 2.1), up to 256 columns (one
+//     chunk: nothing to split) and, up to 2048, from 64 rows per CU (110M token
+//     63.4 / 63.2, 32000 x 768 14.3 / 14.15).  Below 1280 columns 4 x 2 / 2 (9000 x 700
+//     4.65 / 5.2, one 110M layer 5.3 / 7.0, 4 x 4 / 4 5.5; also the tall short ones,
+//     20000 x 300 5.0 / 5.6), to 3072 4 x 4 / 4 (one 2048-wide layer 29.7 / 30.0), to
+//     4096 with 8 rows per CU 4 x 2 / 2 (4096 x 4096 10.3 / 10.7, with 4 wavefronts
+//     10.9), else 2 x 4 / 4 (one 4096-wide layer 111 / 114, 4 x 4 / 4 115; 1024 x
+//     8192 5.9 / 6.5); few rows, fewer per set (300 x 20000 5.9 / 8.8, with 2 rows
+//     7.4, with 4 8.7).
+//   - fp16 (twice the columns and twice the x per load).  Up to 512 columns one
+//     wavefront per set: 8 rows where there are many (20000 x 300 3.9 / 5.4), else
+//     2 (4813 x 385 2.4 / 2.7, 8 rows 2.9).  Below 3840, 4 x 2 / 2 (768 x 768 2.35 /
+//     3.5), 8 rows below 1024 columns and from 32 per CU (8192 x 1000 3.6 / 5.1, 110M
+//     token 34 / 51, 4 rows 38).  From there to 4096 columns whole rows, which take
+//     them in two even rounds of 2048 (4096 x 4096 6.15 / 5.9).  Above, 8 x 4 / 4 (4096
+//     x 11008 14.0 / 16.7, one 4096-wide layer 57.5 / 58.7).  Below 12 rows per CU and
+//     above 1024 columns 2 x 4 / 4 (300 x 20000 5.0 / 8.6, 1024 x 8192 3.4 / 4.0, 3000
+//     x 8000 8.8 / 10.9; 8 rows are 5.3 for the second).
+//   - RMSNorm / SwiGLU, fp32: whole rows up to 1024 columns (2048 x 768 pair 3.9 /
+//     2.9) but for the tall short ones (20000 x 300 pair 4 x 1 / 4 11.5 / 15.9), and
+//     in long launches (20 layers of 1587 columns 443 / 418); below 2048 2 x 1 / 4
+//     (one 110M layer 6.2 / 8.8), else 4 x 4 / 4 (1000 x 8000 pair 11.7 / 19.1, one
+//     70B-shaped layer 495 / 547).  fp16: whole rows from 64 per CU below 2048
+//     columns (110M token 42 / 37), from 32 below 1024 (5312 x 576 pair 5.7 / 4.2) and
+//     near 4096 (three 4096 x 4096 19.0 / 17.5), and in long launches (32 layers
+//     of 1728 columns 362 / 335); up to 512 4 x 1 / 4, below 1024 4 x 2 / 2 (768 x 768
+//     pair 3.25 / 4.6), below 2048 4 x 2 / 4 (4001 x 1501 pair 6.1 / 7.2), else 8 x 2 /
+//     2 (one 70B-shaped layer 250 / 265, 11008 x 4096 pair 30 / 33), with few rows 4 x
+//     4 / 4 (300 x 20000 pair 8.4 / 32, with 8 rows 11.7).
+tvl::RowsSplit rows_split(const tvl_item *items, int32_t n, int cus)
+{
+    const tvl::RowsSplit none;
+    tvl::RowsSplit s;
+    double rows = 0, cells = 0, kcells = 0;
+    for (int32_t i = 0; i < n; ++i) {
+        const tvl_item &t = items[i];
+        if (t.dtype != items[0].dtype) return none;
+        // the kernels address a row set with 32-bit offsets
+        if (t.ldw * elem_size(t.dtype) > (int64_t(1) << 25)) return none;
+        s.fused = s.fused || is_fused(t);
+        const double m = (double)t.M * (t.op == TVL_OP_SWIGLU ? 2 : 1);
+        rows += m;
+        cells += m * (double)t.K;
+        kcells += m * (double)t.K * (double)t.K;
+    }
+    if (n < 1) return none;
+    s.f16 = items[0].dtype == TVL_F16;
+    const double k = kcells / cells, per_cu = rows / cus;
+    auto take = [&](int set, int split, int waves) {
+        s.set = set;
+        s.split = split;
+        s.waves = waves;
+    };
+    if (s.fused && !s.f16) {
+        if (k < 512 && per_cu >= 64)
+            take(4, 1, 4);
+        else if (k <= 1024 || (k < 4096 && per_cu >= 256))
+            return none;
+        else if (k < 2048)
+            take(2, 1, 4);
+        else
+            take(4, 4, 4);
+    } else if (s.fused) {
+        if ((k < 2048 && per_cu >= 64) || (k > 512 && k < 1024 && per_cu >= 32) ||
+            (k >= 3072 && k <= 4096 && per_cu >= 32 && per_cu < 64) || (k < 4096 && per_cu >= 256))
+            return none;
+        else if (k <= 512)
+            take(4, 1, 4);
+        else if (k < 1024)
+            take(4, 2, 2);
+        else if (k < 2048)
+            take(4, 2, 4);
+        else if (per_cu < 8)
+            take(4, 4, 4);
+        else
+            take(8, 2, 2);
+    } else if (!s.f16) {
+        if (k <= 256 || (k <= 768 && per_cu < 8) || (k >= 512 && k < 2048 && per_cu >= 64))
+            return none;
+        else if (k < 1280 || (k >= 3072 && k <= 4096 && per_cu >= 8))
+            take(4, 2, 2);
+        else if (per_cu < 3)
+            take(1, 4, 4);
+        else if (k < 3072 && per_cu >= 4)
+            take(4, 4, 4);
+        else
+            take(2, 4, 4);
+    } else {
+        if (k <= 512)
+            per_cu >= 32 ? take(8, 1, 4) : take(2, 1, 4);
+        else if (k >= 3840 && k <= 4096 && per_cu >= 8)
+            return none;
+        else if (k >= 1024 && per_cu < 12)
+            take(2, 4, 4);
+        else if (k < 3840)
+            k < 1024 && per_cu >= 32 ? take(8, 2, 2) : take(4, 2, 2);
+        else
+            take(8, 4, 4);
+    }
+    // a launch holds less than 2^32 threads
+    double tiles = 0;
+    for (int32_t i = 0; i < n; ++i)
+        tiles += (double)items[i].M / s.rows(items[i].op) + 1;
+    return tiles * s.waves * 64 < 4294967296.0 ? s : none;
+}
+
 // A tuning that chooses the kernel: any field but ksplit, which only says
 // that there is none.
 bool tunes(const tvl_tuning *t)
@@ -821,6 +935,7 @@ tvl_status plan_build(const tvl_item *items, int32_t n, const tvl_tuning *tuning
     p->multiB = multiB;
     p->wmode = f32 && f16 ? 2 : f16 ? 1 : 0;
     if (quant && !tunes(tuning)) p->qsplit = quant_split(items, n, info.cus);
+    if (!multiB && !quant && !tunes(tuning)) p->rsplit = rows_split(items, n, info.cus);
     if (multiB && !tunes(tuning)) p->msplit = multi_split(items, n, info.cus);
     // output rows per tile: a SwiGLU tile streams R rows of W and of W3 per
     // wavefront, i.e. R/2 output rows; a quantised item whose rows share a
@@ -838,6 +953,7 @@ tvl_status plan_build(const tvl_item *items, int32_t n, const tvl_tuning *tuning
     auto rows_of = [&](const tvl_item &t) {
         if (p->qsplit.waves) return p->qsplit.rows();
         if (p->msplit.waves) return p->msplit.rows;
+        if (p->rsplit.waves) return p->rsplit.rows(t.op);
         return (t.op == TVL_OP_SWIGLU ? shape.R / 2 : shape.R) * shape.W * (64 / lanes_of(t));
     };
     // bytes per tile, largest first, so the longest tiles start first
@@ -908,6 +1024,8 @@ tvl_status plan_launch(const tvl_plan *p, hipStream_t st)
     const hipError_t e =
         p->qsplit.waves ? tvl::launch_sweep_quant_split(p->qsplit, p->d_items, p->d_tiles,
                                                         p->ntiles, st)
+        : p->rsplit.waves ? tvl::launch_sweep_rows_split(p->rsplit, p->d_items, p->d_tiles,
+                                                         p->ntiles, st)
         : p->msplit.waves ? tvl::launch_sweep_multi_split(p->msplit, p->d_items, p->d_tiles,
                                                           p->ntiles, st)
         : p->quant  ? tvl::launch_sweep_quant(p->shape, p->d_items, p->d_tiles, p->ntiles, p->grid,
@@ -1050,7 +1168,11 @@ tvl_status gemv_impl(const void *W, int64_t ldw, int32_t dtype, const float *x, 
         if (st != TVL_OK) return st;
     }
     hipError_t e;
-    if (S <= 1) {
+    tvl::RowsSplit rs;
+    if (auto_shape && S <= 1) rs = rows_split(&it, 1, info.cus);
+    if (rs.waves) {
+        e = tvl::launch_item_rows_split(rs, dev_item(it), stream);
+    } else if (S <= 1) {
         e = tvl::launch_gemv_rows(shape, dtype, W, ldw, x, y, (int)M, (int)K, stream);
     } else {
         if (noalloc) {
@@ -1162,8 +1284,11 @@ tvl_status tvl_gemv_item(const tvl_item *item, const tvl_tuning *tuning, hipStre
     if (st != TVL_OK) return st;
     const DevItem d = dev_item(*item);
     tvl::MultiSplitShape ms;
+    tvl::RowsSplit rs;
     if (B && !tunes(tuning)) ms = multi_split(item, 1, info.cus);
-    const hipError_t e = ms.waves ? tvl::launch_item_multi_split(ms, d, stream)
+    if (!B && !tunes(tuning)) rs = rows_split(item, 1, info.cus);
+    const hipError_t e = ms.waves   ? tvl::launch_item_multi_split(ms, d, stream)
+                         : rs.waves ? tvl::launch_item_rows_split(rs, d, stream)
                          : B      ? tvl::launch_item_multi(shape, B, d, stream)
                                   : tvl::launch_item(shape, d, stream);
     if (e != hipSuccess) return fail_hip(e, "item launch");
@@ -1205,6 +1330,7 @@ tvl_status tvl_sweep_plan_info(const tvl_plan *plan, int64_t *ntiles, int64_t *g
     if (rows_per_tile)
         *rows_per_tile = plan->qsplit.waves   ? plan->qsplit.rows()
                          : plan->msplit.waves ? plan->msplit.rows
+                         : plan->rsplit.waves ? plan->rsplit.rows(TVL_OP_GEMV)
                                               : plan->shape.R * plan->shape.W;
     return TVL_OK;
 }

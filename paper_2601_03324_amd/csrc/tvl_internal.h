@@ -153,6 +153,21 @@ hipError_t launch_sweep_quant_split(const QuantSplit &s, const DevItem *items,
                                     const DevTile *tiles, int ntiles, hipStream_t st);
 hipError_t launch_item_quant_split(const QuantSplit &s, const DevItem &item, hipStream_t st);
 
+// One-vector launches of one weight dtype, plain or fused: `split` of a
+// workgroup's `waves` wavefronts share the columns of each `set` weight rows.
+// A launch without the split has waves == 0.
+struct RowsSplit {
+    bool f16 = false;
+    bool fused = false;
+    int set = 0;
+    int split = 0;
+    int waves = 0;
+    int rows(int op) const { return (op == kOpSwiglu ? set / 2 : set) * (waves / split); }
+};
+hipError_t launch_sweep_rows_split(const RowsSplit &s, const DevItem *items, const DevTile *tiles,
+                                   int ntiles, hipStream_t st);
+hipError_t launch_item_rows_split(const RowsSplit &s, const DevItem &item, hipStream_t st);
+
 // LDS bytes for x of K columns in the quantised kernels' layout: whole
 // 1 KiB blocks of 256 columns (the staging loads' unit; the ragged last load
 // of a row reads at most to the end of its 32-column run).

@@ -1,0 +1,187 @@
+"""GPU parity of the column-split one-vector kernels over fp32 and fp16
+weights, plain and with RMSNorm / SwiGLU: every configuration the rule can
+choose, at rows and columns that leave remainders in each of its splits, against
+the oracle and, on exact integer data, bit for bit against the whole-row kernels
+that an explicit tuning selects.
+
+Tolerance: 1e-5 of sum_j |W_ij x_j| (the kernels' bound is (K/256 + 11) 2^-24,
+7.4e-6 at the largest K here); SwiGLU outputs to 1e-5 of what the same relative
+errors of its two sums give.
+"""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_2601_03324_amd import tvl  # noqa: E402
+
+TOL = 1e-5
+DEV = "cuda"
+F32, F16 = tvl.TVL_F32, tvl.TVL_F16
+OLD = dict(rows_per_wave=4, waves_per_block=1, unroll=4, flags=2)
+# (dtype, M, K, rows per tile): 1 x 4 / 4, 2 x 4 / 4, 4 x 4 / 4, 4 x 2 / 2 over
+# fp32; 2 x 1 / 4 (8 rows), 8 x 1 / 4 (32), 4 x 2 / 2, 8 x 2 / 2, 2 x 4 / 4, 8 x 4 / 4 over
+# fp16 (a tile: rows per set times the sets of its workgroup)
+PLAIN = [
+    (F32, 1, 1281, 1), (F32, 7, 28671, 1), (F32, 767, 5123, 1), (F32, 769, 4097, 2),
+    (F32, 1023, 1537, 2), (F32, 1025, 1281, 4), (F32, 1030, 2049, 4), (F32, 2049, 257, 4),
+    (F32, 2051, 1023, 4), (F32, 2049, 4095, 4), (F32, 20001, 511, 4),
+    (F16, 1, 1, 8), (F16, 1003, 511, 8), (F16, 8193, 127, 32), (F16, 9001, 512, 32),
+    (F16, 5, 513, 4), (F16, 3077, 1025, 4), (F16, 3075, 3839, 4), (F16, 8195, 1023, 8),
+    (F16, 3, 28671, 2), (F16, 3071, 2047, 2), (F16, 3079, 4097, 8),
+]
+# outputs per tile of SwiGLU pairs: half the rows of the set
+PAIRS = [
+    (F32, 4099, 511, 8), (F32, 3, 1025, 4), (F32, 67, 2047, 4), (F32, 5, 2049, 2),
+    (F32, 301, 11009, 2),
+    (F16, 1, 1, 8), (F16, 77, 512, 8), (F16, 9, 515, 2), (F16, 70, 1023, 2), (F16, 35, 1601, 4),
+    (F16, 9, 2049, 2), (F16, 1027, 2051, 4), (F16, 7, 20481, 2),
+]
+
+
+def name(c):
+    return f"{'f32' if c[0] == F32 else 'f16'}-{c[1]}x{c[2]}"
+
+
+def weights(rng, M, K, dt, exact):
+    Wf = rng.integers(-3, 4, (M, K)) if exact else rng.standard_normal((M, K)) * 0.02
+    Wf = Wf.astype(np.float32)
+    return Wf if dt == F32 else synth.f32_to_f16_bits(Wf)
+
+
+def on_gpu(host, dt, pad=0):
+    """Rows of the minimal stride plus `pad` lines, NaN in the padding."""
+    M, K = host.shape
+    ldw = tvl.tvl_row_stride(K, dt) + pad * (32 if dt == F32 else 64)
+    buf = torch.full((M, ldw), float("nan"), dtype=torch.float32 if dt == F32 else torch.float16,
+                     device=DEV)
+    host = np.ascontiguousarray(host)
+    buf[:, :K] = torch.from_numpy(host if dt == F32 else host.view(np.float16)).to(DEV)
+    return buf, ldw
+
+
+def vec(v):
+    """K floats ending the allocation at K rounded up to 16 bytes, NaN after."""
+    K = len(v)
+    d = torch.full(((K + 3) // 4 * 4,), float("nan"), device=DEV)
+    d[:K] = torch.from_numpy(v).to(DEV)
+    return d
+
+
+def out(M):
+    return torch.full((M + 5,), -12345.0, device=DEV)
+
+
+def sums(W, x, dt):
+    return (oracle.gemv_f32 if dt == F32 else oracle.gemv_f16)(W, x)
+
+
+@pytest.mark.parametrize("case", PLAIN, ids=name)
+def test_plain_configurations(case):
+    dt, M, K, rows = case
+    print(f"rows split {M}x{K} dtype={dt}", flush=True)
+    rng = np.random.default_rng(M * 31 + K * 7)
+    for exact in (True, False):
+        W = weights(rng, M, K, dt, exact)
+        x = (rng.integers(-3, 4, K) if exact else rng.standard_normal(K)).astype(np.float32)
+        buf, ldw = on_gpu(W, dt, pad=int(exact))
+        xd, y, one, old = vec(x), out(M), out(M), out(M)
+        plan = tvl.tvl_sweep_plan_create([(buf, ldw, xd, y, M, K, dt)])
+        plan.run()
+        tvl.tvl_gemv_item(tvl.item(buf, ldw, xd, one, M, K, dt))
+        tvl.tvl_gemv_ex(buf, ldw, dt, xd, old, M, K, OLD)
+        torch.cuda.synchronize()
+        assert bool((y[M:] == -12345.0).all()) and bool((one[M:] == -12345.0).all())
+        assert plan.info()["rows_per_tile"] == rows
+        if M > 128:  # (few long rows: the single call splits K over workgroups)
+            assert torch.equal(y, one)
+        if exact:  # |sums| below 2^24: no order of summation rounds
+            assert torch.equal(y, old) and torch.equal(one, old)
+            continue
+        yref, S = sums(W, x, dt)
+        for got in (y, one):
+            r = oracle.check(got[:M].cpu().numpy(), yref, S, TOL)
+            assert r["bad"] == 0, r
+
+
+def pair_reference(W, W3, x, g, eps, dt):
+    """silu(a) b with its scale: |silu'| <= 1.1 and |silu(a)| <= |a| carry the
+    two sums' errors."""
+    n = x.astype(np.float64)
+    if g is not None:
+        n = n * g / np.sqrt(np.mean(n * n) + np.float32(eps))
+    to64 = lambda m: (m if dt == F32 else m.view(np.float16)).astype(np.float64)  # noqa: E731
+    A, B = to64(W), to64(W3)
+    a, b = A @ n, B @ n
+    Sa, Sb = np.abs(A) @ np.abs(n), np.abs(B) @ np.abs(n)
+    return a / (1 + np.exp(-a)) * b, 1.1 * Sa * np.abs(b) + np.abs(a) * Sb
+
+
+@pytest.mark.parametrize("norm", [False, True], ids=["pair", "norm"])
+@pytest.mark.parametrize("case", PAIRS, ids=name)
+def test_fused_configurations(case, norm):
+    """A SwiGLU pair, and in the same launch a GEMV item of the same rows with
+    the same RMSNorm."""
+    dt, M, K, rows = case
+    print(f"rows split pair {M}x{K} dtype={dt} norm={norm}", flush=True)
+    rng = np.random.default_rng(M * 31 + K * 7 + norm)
+    W, W3 = (weights(rng, M, K, dt, False) for _ in range(2))
+    x = rng.standard_normal(K).astype(np.float32)
+    g = (1 + 0.1 * rng.standard_normal(K)).astype(np.float32) if norm else None
+    (wd, ldw), (w3d, _) = on_gpu(W, dt, 1), on_gpu(W3, dt, 1)
+    xd, y, yg, one = vec(x), out(M), out(M), out(M)
+    kw = dict(g=vec(g) if norm else None, eps=1e-5 if norm else 0.0)
+    pair = dict(W=wd, ldw=ldw, x=xd, y=y, M=M, K=K, dtype=dt, op=tvl.TVL_OP_SWIGLU, W3=w3d, **kw)
+    alone = tvl.tvl_sweep_plan_create([pair])
+    assert alone.info()["rows_per_tile"] == 2 * rows  # (of a GEMV item)
+    plan = tvl.tvl_sweep_plan_create([pair, dict(W=wd, ldw=ldw, x=xd, y=yg, M=M, K=K, dtype=dt, **kw)])
+    plan.run()
+    tvl.tvl_gemv_item(dict(pair, y=one))
+    torch.cuda.synchronize()
+    ref, S = pair_reference(W, W3, x, g, 1e-5, dt)
+    for got in (y, one):
+        assert bool((got[M:] == -12345.0).all())
+        err = np.abs(got[:M].cpu().numpy().astype(np.float64) - ref)
+        assert np.all(err <= TOL * S + 1e-12), (err / S).max()
+    assert bool((yg[M:] == -12345.0).all())
+    xn = x.astype(np.float64)
+    if norm:
+        xn = xn * g / np.sqrt(np.mean(xn * xn) + np.float32(1e-5))
+    Wd = (W if dt == F32 else W.view(np.float16)).astype(np.float64)
+    err = np.abs(yg[:M].cpu().numpy().astype(np.float64) - Wd @ xn)
+    S = np.abs(Wd) @ np.abs(xn)
+    assert np.all(err <= TOL * S), (err / S).max()
+
+
+@pytest.mark.parametrize("dt", [F32, F16], ids=["f32", "f16"])
+def test_plan_of_ragged_items(dt):
+    """Items of different sizes share one configuration, plain and fused."""
+    for fused in (False, True):
+        items, keep = [], []
+        for i, (M, K) in enumerate(((1, 1), (130, 768), (17, 2777), (257, 1640), (3, 5000), (64, 65))):
+            rng = np.random.default_rng(7 * i + dt)
+            W, x = weights(rng, M, K, dt, False), rng.standard_normal(K).astype(np.float32)
+            g = np.full(K, 2.0, np.float32) if fused and i % 2 else None
+            (buf, ldw), xd, y = on_gpu(W, dt, i % 2), vec(x), out(M)
+            items.append(dict(W=buf, ldw=ldw, x=xd, y=y, M=M, K=K, dtype=dt,
+                              g=None if g is None else vec(g), eps=0.0))
+            keep.append((W, x, g, y, items[-1]))
+        tvl.tvl_sweep_plan_create(items).run()
+        torch.cuda.synchronize()
+        for W, x, g, y, it in keep:
+            M = it["M"]
+            if g is not None:
+                x = (x * (2 / np.sqrt(np.mean(x.astype(np.float64) ** 2)))).astype(np.float32)
+            yref, S = sums(W, x, dt)
+            r = oracle.check(y[:M].cpu().numpy(), yref, S, TOL)
+            assert r["bad"] == 0, (W.shape, fused, r)
+            assert bool((y[M:] == -12345.0).all())
