@@ -446,6 +446,13 @@ Shape default_quant_shape(double qbytes, bool q4, int64_t kq)
 //     four chunks per row are left and no row pads past 5/4 of its loads
 //     (4096 x 4096, 8-bit: 5.7 us with 32 lanes against 6.1 with 16; 1024 x
 //     8192: 4.3 with 64 against 7.0).
+//   - Long rows whose sets fill the CUs evenly in one or two rounds (90 % of
+//     their places): eight wavefronts per set and the fewest lanes that do, so
+//     x is read from LDS by more rows: each wavefront needs a chunk (8-bit, with
+//     half the decode per byte, four).  4-bit 4096 x 11008 6.9 against 7.5, 4000 x
+//     28672 11.9 against 17.3, 2048 x 8192 3.6 against 4.1, 8192 x 8192 7.8 against
+//     8.7; 8-bit 4096 x 11008 8.7 against 10.5.  Uneven, it loses (12000 x 8000, 4
+//     bits, 16 lanes 11.5, 8 12.1, against 11.1).
 tvl::QuantSplit quant_split(const tvl_item *items, int32_t n, int cus)
 {
     tvl::QuantSplit s;
@@ -466,6 +473,21 @@ tvl::QuantSplit quant_split(const tvl_item *items, int32_t n, int cus)
     if (waves() >= 12.0 * cus && kmean < (s.bits == 8 ? 2048.0 : 8192.0)) {
         s.waves = s.bits == 8 ? 4 : 2;
         return s;
+    }
+    for (int g = s.lanes; g <= 32; g *= 2) {
+        int64_t tiles = 0, kmin = kMaxQuantK;
+        for (int32_t i = 0; i < n; ++i) {
+            tiles += (items[i].M + 256 / g - 1) / (256 / g);
+            kmin = std::min<int64_t>(kmin, items[i].K);
+        }
+        const double rounds = (double)tiles / cus;
+        const int64_t chunk = (int64_t)g * (128 / s.bits);
+        if (kmin >= chunk * (s.bits == 8 ? 32 : 8) &&
+            ((rounds >= 0.9 && rounds <= 1.0) || (rounds >= 1.8 && rounds <= 2.0))) {
+            s.lanes = g;
+            s.split = s.waves = 8;
+            return s;
+        }
     }
     s.split = s.waves = 4;
     while (s.lanes < 64 && waves() < (s.bits == 8 ? 12.0 : 8.0) * cus) {

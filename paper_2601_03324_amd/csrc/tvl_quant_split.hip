@@ -242,7 +242,8 @@ struct InstSplit {
 // (bits, lanes per row, wavefronts per row set, wavefronts per workgroup)
 #define TVL_SPLIT_SHAPES(X)                                                                       \
     X(8, 16, 2, 4) X(8, 16, 4, 4) X(8, 32, 4, 4) X(8, 64, 4, 4) X(4, 8, 2, 2) X(4, 8, 4, 4)       \
-    X(4, 16, 4, 4) X(4, 32, 4, 4) X(4, 64, 4, 4)
+    X(4, 16, 4, 4) X(4, 32, 4, 4) X(4, 64, 4, 4) X(8, 16, 8, 8) X(8, 32, 8, 8) X(4, 8, 8, 8)       \
+    X(4, 16, 8, 8) X(4, 32, 8, 8)
 
 hipError_t launch_sweep_quant_split(const QuantSplit &s, const DevItem *items,
                                     const DevTile *tiles, int ntiles, hipStream_t st)

@@ -35,6 +35,10 @@ CASES = [
     (tvl.TVL_Q4, 1, 1, 32), (tvl.TVL_Q4, 37, 1023, 32), (tvl.TVL_Q4, 66, 1601, 32),
     (tvl.TVL_Q4, 18, 2049, 16), (tvl.TVL_Q4, 35, 3967, 16),
     (tvl.TVL_Q4, 10, 4097, 8), (tvl.TVL_Q4, 7, 8193, 4), (tvl.TVL_Q4, 5, 28671, 4),
+    # eight wavefronts per set: 16 and 32 lanes (8-bit); 8, 16 and 32 (4-bit)
+    (tvl.TVL_Q8, 3701, 8200, 16), (tvl.TVL_Q8, 1849, 16389, 8),
+    (tvl.TVL_Q4, 7403, 2049, 32), (tvl.TVL_Q4, 14747, 2111, 32), (tvl.TVL_Q4, 3701, 4099, 16),
+    (tvl.TVL_Q4, 1849, 8195, 8),
 ]
 
 
