@@ -453,7 +453,7 @@ Shape default_quant_shape(double qbytes, bool q4, int64_t kq)
 //     28672 11.9 against 17.3, 2048 x 8192 3.6 against 4.1, 8192 x 8192 7.8 against
 //     8.7; 8-bit 4096 x 11008 8.7 against 10.5.  Uneven, it loses (12000 x 8000, 4
 //     bits, 16 lanes 11.5, 8 12.1, against 11.1).
-tvl::QuantSplit quant_split(const tvl_item *items, int32_t n, int cus)
+tvl::QuantSplit quant_split_shape(const tvl_item *items, int32_t n, int cus)
 {
     tvl::QuantSplit s;
     double codes = 0, kcodes = 0, rows = 0;
@@ -499,6 +499,17 @@ tvl::QuantSplit quant_split(const tvl_item *items, int32_t n, int cus)
         s.lanes = g;
     }
     return s;
+}
+
+// ... unless that would be 2^32 threads or more, which no launch holds (the
+// whole-row forms have up to 128 rows per 256 threads): waves == 0 then.
+tvl::QuantSplit quant_split(const tvl_item *items, int32_t n, int cus)
+{
+    const tvl::QuantSplit s = quant_split_shape(items, n, cus);
+    double tiles = 0;
+    for (int32_t i = 0; i < n && s.waves; ++i)
+        tiles += (double)items[i].M / s.rows() + 1;
+    return tiles * s.waves * 64 < 4294967296.0 ? s : tvl::QuantSplit{};
 }
 
 // Several-vector launches of one weight dtype take the column split
@@ -1137,10 +1148,11 @@ tvl_status gemv_impl(const void *W, int64_t ldw, int32_t dtype, const float *x, 
             st = noalloc_setup(qdev, stream, &p, &c);
             if (st != TVL_OK) return st;
         }
-        const hipError_t qe =
-            tunes(tuning)
-                ? tvl::launch_item_quant(qs, dev_item(it), qxbytes, stream)
-                : tvl::launch_item_quant_split(quant_split(&it, 1, qinfo.cus), dev_item(it), stream);
+        const tvl::QuantSplit split =
+            tunes(tuning) ? tvl::QuantSplit{} : quant_split(&it, 1, qinfo.cus);
+        const hipError_t qe = split.waves
+                                  ? tvl::launch_item_quant_split(split, dev_item(it), stream)
+                                  : tvl::launch_item_quant(qs, dev_item(it), qxbytes, stream);
         if (qe != hipSuccess) return fail_hip(qe, "quantised gemv launch");
         return TVL_OK;
     }
