@@ -47,7 +47,8 @@ CSRC = os.path.join(ROOT, "paper_2601_03324_amd", "csrc")
 # The sources each workload's dominant kernel is compiled from: the shared
 # declarations and device code, plus its family's translation unit.
 KERNEL_COMMON = ("tvl_internal.h", "tvl_device.h")
-KERNEL_FAMILY = {"fused110m": "tvl_fused.hip", "fused70b8": "tvl_fused.hip",
+KERNEL_FAMILY = {"fused110m": "tvl_fused.hip", "fused70b8": "tvl_rows_split.hip",
+                 "sweep7b": "tvl_rows_split.hip", "stack70b8": "tvl_rows_split.hip",
                  "beam4_110m": "tvl_multi_split.hip", "beam8_110m": "tvl_multi.hip",
                  "beam16_110m": "tvl_multi.hip", "beam8_70b": "tvl_multi.hip",
                  "beam16_70b": "tvl_multi.hip"}

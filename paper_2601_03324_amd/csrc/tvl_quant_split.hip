@@ -7,8 +7,8 @@
 // (~2 per code), and in short ones the latency of a wavefront's dependent
 // loads, so a launch needs many wavefronts with little to do each.  With whole
 // rows per wavefront a 4096 x 11008 4-bit matrix had 16 workgroups of 43
-// dependent rounds (88 us); with the columns split over four wavefronts it has
-// 512 of 3 rounds (8.6 us).  A split also makes x cheap: each wavefront copies
+// dependent rounds (88 us); with the columns split over eight wavefronts it has
+// 256 of 3 rounds (6.9 us).  A split also makes x cheap: each wavefront copies
 // just its own chunk's x into LDS (1-4 coalesced loads, no workgroup barrier),
 // where direct x costs as many load instructions as the codes.  So does the
 // register budget: x takes registers only while a chunk is decoded, which
